@@ -48,6 +48,8 @@ constexpr int kLdsMaxBytes = 64 * 1024;  // lds_run: whole surface in LDS
 constexpr int kGraphSweeps = 32;
 constexpr long long kNoEnd = 0x7FFFFFFFFFFFFFFFll;  // t_end of a surface with no bound
 constexpr int kPsGrid = 2048;       // workgroups of the power-sum reduction
+constexpr size_t kStagingBytes = 4096;      // least size of a pinned staging buffer
+constexpr long long kReadRecords = 1 << 15; // most log records copied at once (768 KiB pinned)
 
 // ---------------------------------------------------------------------------
 // Block-kernel variants.  The tile block shape never changes results; it
@@ -259,9 +261,20 @@ struct Staging {
         if (n > bytes) {
             if (host) HIP_TRY(hipHostFree(host));
             host = nullptr;
+            n = std::max(n, kStagingBytes);
             HIP_TRY(hipHostMalloc(&host, n, hipHostMallocDefault));
             bytes = n;
         }
+        return RSOS_OK;
+    }
+    // Copies n bytes from the device into the buffer and waits for them and
+    // for everything before them on the stream.
+    rsos_status copy_from(const void *dev, size_t n, hipStream_t st)
+    {
+        rsos_status r = ensure(n);
+        if (r != RSOS_OK) return r;
+        HIP_TRY(hipMemcpyAsync(host, dev, n, hipMemcpyDeviceToHost, st));
+        HIP_TRY(hipStreamSynchronize(st));
         return RSOS_OK;
     }
     rsos_status copy_to(void *dev, size_t n, hipStream_t st)
@@ -318,6 +331,7 @@ struct SurfaceGroup {
     long long *d_acc = nullptr;        // kAccWords per block-path surface
     std::vector<int32_t *> readout;    // 16-bit storage: int32[L^2] device scratch per surface
     long long *d_ps = nullptr;         // power sums: per-workgroup partials, then the result
+    long long *d_rec = nullptr;        // the surfaces' current records (read_widths)
     int xmode = 1;                     // workgroup -> block order (rsosk::block_map) without a choice
     std::vector<Shape> shapes;         // block-path surfaces by kernel instance
     std::vector<Choice> want;          // per surface: a tuned launch choice (or none); read by setup()
@@ -558,21 +572,36 @@ struct SurfaceGroup {
                         t_from + n, t0[i], s.t);
         if (t_from + s.log_cap <= s.t && n > 0)
             return fail(RSOS_E_INVAL, "records before t=%lld are no longer kept", s.t - s.log_cap + 1);
-        HIP_TRY(hipStreamSynchronize(stream));
-        std::vector<long long> buf((size_t)(3 * std::max<long long>(n, 1)));
-        for (long long k = 0; k < n;) {
-            const long long slot = (t_from + k) % s.log_cap;
-            const long long run = std::min(n - k, s.log_cap - slot);
-            HIP_TRY(hipMemcpy(buf.data() + 3 * k, s.log + 3 * slot, sizeof(long long) * 3 * run,
-                              hipMemcpyDeviceToHost));
-            k += run;
+        if (n == 0) {
+            HIP_TRY(hipStreamSynchronize(stream));
+            return RSOS_OK;
         }
-        for (long long k = 0; k < n; ++k) {
-            out[k].t = t_from + k;
-            out[k].s1 = buf[3 * k];
-            out[k].s2 = buf[3 * k + 1];
-            out[k].accepted = buf[3 * k + 2];
-            out[k].w2 = w2_of(s.L, out[k].s1, out[k].s2);
+        for (long long k = 0; k < n;) {
+            const long long slot = (t_from + k) % s.log_cap, run = std::min({n - k, s.log_cap - slot, kReadRecords});
+            rsos_status st = staging.copy_from(s.log + 3 * slot, sizeof(long long) * 3 * run, stream);
+            if (st != RSOS_OK) return st;
+            const long long *r = (const long long *)staging.host;
+            for (long long i = 0; i < run; ++i, ++k)
+                out[k] = {t_from + k, r[3 * i], r[3 * i + 1], r[3 * i + 2], w2_of(s.L, r[3 * i], r[3 * i + 1])};
+        }
+        return RSOS_OK;
+    }
+
+    // The current record of every surface: gathered into one array on the
+    // device and copied once (one copy per surface cost about 12 us each,
+    // 3 ms of a 256-surface call).
+    rsos_status read_widths(rsos_width_t *out)
+    {
+        const int n = (int)host.size();
+        rsos_status st;
+        if (!d_rec && (st = dev_alloc((void **)&d_rec, sizeof(long long) * 3 * n)) != RSOS_OK) return st;
+        hipLaunchKernelGGL(rsosk::gather_records, dim3((unsigned)(n + 255) / 256), dim3(256), 0, stream, d_desc, n, d_rec);
+        HIP_TRY(hipGetLastError());
+        if ((st = staging.copy_from(d_rec, sizeof(long long) * 3 * n, stream)) != RSOS_OK) return st;
+        const long long *r = (const long long *)staging.host;
+        for (int k = 0; k < n; ++k) {
+            const SurfDev &s = host[rows[k]];
+            out[rows[k]] = {s.t, r[3 * k], r[3 * k + 1], r[3 * k + 2], w2_of(s.L, r[3 * k], r[3 * k + 1])};
         }
         return RSOS_OK;
     }
@@ -1061,11 +1090,7 @@ rsos_status rsos_batch_width(rsos_batch *b, rsos_width_t *out)
 {
     CHECK_HANDLE(b, b->g);
     if (!out) return fail(RSOS_E_INVAL, "out is NULL");
-    for (size_t i = 0; i < b->g.host.size(); ++i) {
-        rsos_status st = mark(b->g, b->g.read_log((int)i, b->g.host[i].t, 1, out + i));
-        if (st != RSOS_OK) return st;
-    }
-    return RSOS_OK;
+    return mark(b->g, b->g.read_widths(out));
 }
 
 rsos_status rsos_batch_log(rsos_batch *b, int32_t i, int64_t t_from, int64_t n, rsos_width_t *out)

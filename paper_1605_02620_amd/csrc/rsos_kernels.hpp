@@ -1122,6 +1122,17 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WideOcc<D, T
                                                                      &s_bad, ca, cs2, b);
 }
 
+// The record (S1, S2, A) of every surface's current time: out[3 k] for row k
+// of the descriptor table.
+__global__ void gather_records(const SurfDev *__restrict__ descs, int n, long long *__restrict__ out)
+{
+    const int k = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (k >= n) return;
+    const SurfDev &d = descs[k];
+    const long long *r = d.log + 3 * (d.t % d.log_cap);
+    for (int i = 0; i < 3; ++i) out[3 * k + i] = r[i];
+}
+
 // Conversions between int32 heights and 16-bit residues (grid-stride).
 __global__ void pack16(const int32_t *__restrict__ src, uint16_t *__restrict__ dst, long long n)
 {

@@ -40,7 +40,6 @@ struct MsDev {
     long long *log;       // [G][128][log_cap][3]: (S1, S2, A) of time tau at slot tau % log_cap
     long long *t;         // [G] sweeps done
     long long log_cap;
-    long long t_end;
     unsigned long long seed;
     int L, N, T, G, nchunk;
 };
@@ -83,7 +82,6 @@ __global__ __launch_bounds__(64) void ms_phase(const MsDev *__restrict__ dp, int
     const long long tv = d.t[g];
     const long long t = (long long)(((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(tv >> 32)) << 32) |
                                     (uint32_t)__builtin_amdgcn_readfirstlane((int)tv));
-    if (t >= d.t_end) return;
     const int ty = k / (T / 2), tx = 2 * (k % (T / 2)) + ((ty + p) & 1);
     const unsigned long long key = d.seed + (unsigned long long)g;
     const uint32_t k0 = (uint32_t)key, k1 = (uint32_t)(key >> 32);
@@ -211,7 +209,6 @@ __global__ __launch_bounds__(128) void ms_phase_b(const MsDev *__restrict__ dp, 
     const long long tv = d.t[g];
     const long long t = (long long)(((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(tv >> 32)) << 32) |
                                     (uint32_t)__builtin_amdgcn_readfirstlane((int)tv));
-    if (t >= d.t_end) return;
     const int ty = k / (T / 2), tx = 2 * (k % (T / 2)) + ((ty + p) & 1);
     const unsigned long long key = d.seed + (unsigned long long)g;
     const uint32_t k0 = (uint32_t)key, k1 = (uint32_t)(key >> 32);
@@ -358,7 +355,6 @@ __global__ __launch_bounds__(kMsSub * kMsReal) void ms_partial(const MsDev *__re
     const int c = blockIdx.x, g = blockIdx.y;
     const int sub = threadIdx.x / kMsReal, r = threadIdx.x % kMsReal;
     const long long t = d.t[g];
-    if (t >= d.t_end) return;
     const long long tiles = (long long)d.T * d.T;
     const long long cs = (tiles + d.nchunk - 1) / d.nchunk;
     const long long lo = c * cs, hi = min(tiles, lo + cs);
@@ -406,6 +402,16 @@ __global__ __launch_bounds__(kMsSub * kMsReal) void ms_partial(const MsDev *__re
         // every workgroup of the group read t before it was counted
         d.t[g] = t + 1;
     }
+}
+
+// The record (S1, S2, A) of time t of every realization.
+__global__ void ms_gather_records(const MsDev *__restrict__ dp, int n, long long t, long long *__restrict__ out)
+{
+    const MsDev &d = *dp;
+    const int k = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (k >= n) return;
+    const long long *r = d.log + ((long long)k * d.log_cap + t % d.log_cap) * 3;
+    for (int i = 0; i < 3; ++i) out[3 * k + i] = r[i];
 }
 
 // Realization r of group g as int32 heights (grid-stride).
