@@ -140,7 +140,9 @@ bool variant_fits(const Variant &v, int L, int N, bool packed, bool dt = false)
     const int T = L / v.D;
     const int rw = v.TX * v.D + 2 * (v.D + 1), rh = v.TY * v.D + 2 * (v.D + 1);
     const int rwl = packed ? (rw + 14) & ~7 : (rw + 6) & ~3;
-    if (T % v.TX != 0 || T % v.TY != 0 || rh > L) return false;
+    if (T < v.TX || T < v.TY || rh > L) return false;
+    // 16-bit storage keeps to the lattices that the shape tiles
+    if (packed && (T % v.TX != 0 || T % v.TY != 0)) return false;
     // a region wider than the lattice only for a block as wide as the
     // lattice (its ring columns are copies of its own far edge, recomputed
     // from the same inputs)
@@ -157,13 +159,22 @@ bool variant_fits(const Variant &v, int L, int N, bool packed, bool dt = false)
     return true;
 }
 
-// First fitting variant for D that fits every (L, N) (optionally forced by
-// the RSOS_VARIANT environment variable "TXxTYxNTxELEM", e.g. "16x8x128x2";
-// ELEM is 16 for the 16-bit storage kernels).
+// Blocks of a variant along one side of T tiles.
+int blocks_along(int T, int tiles) { return (T + tiles - 1) / tiles; }
+
+// The variant for D without a tuned choice: the first one that fits every
+// (L, N) and sweeps at most 4/3 of its tiles (blocks that overlap at the
+// lattice's edges sweep tiles twice; the variants' own times differ by less
+// than that), else the fitting one that stages the fewest sites.
+// (Optionally forced by the RSOS_VARIANT environment variable
+// "TXxTYxNTxELEM", e.g. "16x8x128x2"; ELEM is 16 for the 16-bit storage
+// kernels.)
 const Variant *pick_variant(int D, const std::vector<std::pair<int, int>> &LN, bool packed = false,
                             bool dt = false)
 {
     const char *force = getenv("RSOS_VARIANT");
+    const Variant *least = nullptr;
+    double least_staged = 0;
     for (const Variant &v : kVariants) {
         if (v.D != D) continue;
         if (force) {
@@ -172,10 +183,22 @@ const Variant *pick_variant(int D, const std::vector<std::pair<int, int>> &LN, b
             if (strcmp(force, want) != 0) continue;
         }
         bool ok = true;
-        for (auto &ln : LN) ok = ok && variant_fits(v, ln.first, ln.second, packed, dt);
-        if (ok) return &v;
+        double tiles = 0, blocks = 0;
+        for (auto &ln : LN) {
+            ok = ok && variant_fits(v, ln.first, ln.second, packed, dt);
+            const int T = ln.first / D;
+            tiles += (double)T * T;
+            blocks += (double)blocks_along(T, v.TX) * blocks_along(T, v.TY);
+        }
+        if (!ok) continue;
+        if (3 * blocks * v.TX * v.TY <= 4 * tiles) return &v;
+        const double staged = blocks * (v.TX * D + 2 * (D + 1)) * (v.TY * D + 2 * (D + 1));
+        if (!least || staged < least_staged) {
+            least = &v;
+            least_staged = staged;
+        }
     }
-    return nullptr;
+    return least;
 }
 
 bool uses_lds(int L);
@@ -409,8 +432,8 @@ struct SurfaceGroup {
             for (int i : members[g]) {
                 SurfDev &sd = host[i];
                 const int T = sd.L / D;
-                sd.nbx = T / sh.variant->TX;
-                sd.nblocks = sd.nbx * (T / sh.variant->TY);
+                sd.nbx = blocks_along(T, sh.variant->TX);
+                sd.nblocks = sd.nbx * blocks_along(T, sh.variant->TY);
                 sd.block_start = (int)blocks;
                 blocks += sd.nblocks;
                 if (blocks > (1ll << 30)) return fail(RSOS_E_INVAL, "too many tile blocks");
@@ -1240,8 +1263,8 @@ extern "C" rsos_status rsos_sweep_static(const rsos_params *p, int32_t *d_h, int
     if (!uses_lds(p->L)) {
         v = pick_variant(D, {{p->L, p->N}}, false, sched == 1);
         if (!v) return fail(RSOS_E_INVAL, "no tile-block shape fits L=%d, N=%d, D=%d", p->L, p->N, D);
-        d.nbx = d.T / v->TX;
-        d.nblocks = d.nbx * (d.T / v->TY);
+        d.nbx = blocks_along(d.T, v->TX);
+        d.nblocks = d.nbx * blocks_along(d.T, v->TY);
         d.block_start = 0;
     }
     hipStream_t s = (hipStream_t)stream;
