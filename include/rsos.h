@@ -211,7 +211,7 @@ rsos_status rsos_timing_read(rsos_surface *s, int64_t *launches, double *mean_ms
  * "block_sweep<8,32,8,256,int8,int16,0>" (D, tiles per block in x and y,
  * threads, LDS element type, the wider type of blocks that do not fit it,
  * schedule), "block_sweep16<8,32,8,256,0>" with 16-bit storage, or
- * "lds_run<8,256,0>" for an LDS-resident surface; written NUL-terminated
+ * "lds_run<8,512,0>" for an LDS-resident surface; written NUL-terminated
  * into buf (at most len bytes).  With several kernel instances (a tuned
  * batch) the first one. */
 rsos_status rsos_kernel_name(rsos_surface *s, char *buf, int32_t len);

@@ -44,7 +44,7 @@ namespace {
         if (e_ != hipSuccess) return fail(RSOS_E_DEVICE, "%s: %s", #expr, hipGetErrorString(e_)); \
     } while (0)
 
-constexpr int kLdsMaxBytes = 64 * 1024;  // lds_run: whole surface in LDS
+constexpr int kLdsMaxBytes = 64 * 1024;  // surfaces of at most this many bytes of int32 run whole in LDS
 constexpr int kGraphSweeps = 32;
 constexpr long long kNoEnd = 0x7FFFFFFFFFFFFFFFll;  // t_end of a surface with no bound
 constexpr int kPsGrid = 2048;       // workgroups of the power-sum reduction
@@ -217,11 +217,14 @@ rsos_status check_packed(const rsos_params *p)
     return RSOS_OK;
 }
 
-typedef void (*LdsLaunch)(dim3, size_t, hipStream_t, SurfDev *, const int *);
+// Surfaces that live in LDS: lds_run, or lds_run32 (wide) where a
+// restriction of the launch exceeds the 16-bit staging.
+typedef void (*LdsLaunch)(dim3, size_t, bool, hipStream_t, SurfDev *, const int *);
 template <int D, int SCHED>
-void launch_lds(dim3 grid, size_t shm, hipStream_t st, SurfDev *d, const int *w)
+void launch_lds(dim3 grid, size_t shm, bool wide, hipStream_t st, SurfDev *d, const int *w)
 {
-    hipLaunchKernelGGL((rsosk::lds_run<D, 256, SCHED>), grid, dim3(256), shm, st, d, w);
+    if (wide) hipLaunchKernelGGL((rsosk::lds_run32<D, 256, SCHED>), grid, dim3(256), shm, st, d, w);
+    else hipLaunchKernelGGL((rsosk::lds_run<D, rsosk::kLdsThreads, SCHED>), grid, dim3(rsosk::kLdsThreads), shm, st, d, w);
 }
 LdsLaunch lds_launcher(int D, int sched = 0)
 {
@@ -240,6 +243,32 @@ LdsLaunch lds_launcher(int D, int sched = 0)
     case 32: return launch_lds<32, 0>;
     }
     return nullptr;
+}
+
+bool lds_wide(int L, int N) { return (long long)N * L > rsosk::kLdsRunMaxNL; }
+
+// LDS of one workgroup that runs a surface of side L.
+size_t lds_bytes_of(int D, int sched, int L, bool wide)
+{
+    if (wide) return (size_t)L * L * 4;
+    const int ph = sched == 1 ? 4 : 2;
+    switch (D) {
+    case 2: return (size_t)rsosk::LdsRun<2>::bytes(L, ph);
+    case 4: return (size_t)rsosk::LdsRun<4>::bytes(L, ph);
+    case 8: return (size_t)rsosk::LdsRun<8>::bytes(L, ph);
+    case 16: return (size_t)rsosk::LdsRun<16>::bytes(L, ph);
+    }
+    return (size_t)rsosk::LdsRun<32>::bytes(L, ph);
+}
+
+// The (L, N) of the surfaces of one launch: whether it takes the wide
+// kernel, and the LDS of its workgroups.
+void lds_plan(int D, int sched, const std::vector<std::pair<int, int>> &LN, bool *wide, size_t *bytes)
+{
+    *wide = false;
+    for (auto &x : LN) *wide = *wide || lds_wide(x.first, x.second);
+    *bytes = 0;
+    for (auto &x : LN) *bytes = std::max(*bytes, lds_bytes_of(D, sched, x.first, *wide));
 }
 
 bool valid_D(int D) { return D == 2 || D == 4 || D == 8 || D == 16 || D == 32; }
@@ -363,6 +392,7 @@ struct SurfaceGroup {
     int *d_lds_idx = nullptr;
     int graph_k = kGraphSweeps;        // sweeps per captured graph
     size_t lds_bytes = 0;
+    bool lds_is_wide = false;
     Staging staging;
     hipGraphExec_t graph = nullptr;
     int graph_sweeps = 0;
@@ -473,9 +503,9 @@ struct SurfaceGroup {
             std::vector<int> pos(lds_idx.size());
             for (size_t k = 0; k < pos.size(); ++k) pos[k] = nblk_rows + (int)k;
             HIP_TRY(hipMemcpy(d_lds_idx, pos.data(), sizeof(int) * pos.size(), hipMemcpyHostToDevice));
-            int maxL = 0;
-            for (int i : lds_idx) maxL = std::max(maxL, host[i].L);
-            lds_bytes = (size_t)maxL * maxL * 4;
+            std::vector<std::pair<int, int>> ln;
+            for (int i : lds_idx) ln.push_back({host[i].L, host[i].N});
+            lds_plan(D, sched, ln, &lds_is_wide, &lds_bytes);
         }
         return upload_all();
     }
@@ -515,7 +545,7 @@ struct SurfaceGroup {
     {
         if (n <= 0) return RSOS_OK;
         if (!lds_idx.empty()) {
-            lds_launcher(D, sched)(dim3((unsigned)lds_idx.size()), lds_bytes, stream, d_desc, d_lds_idx);
+            lds_launcher(D, sched)(dim3((unsigned)lds_idx.size()), lds_bytes, lds_is_wide, stream, d_desc, d_lds_idx);
             HIP_TRY(hipGetLastError());
         }
         if (blk_idx.empty()) return RSOS_OK;
@@ -974,7 +1004,7 @@ rsos_status rsos_kernel_name(rsos_surface *s, char *buf, int32_t len)
         snprintf(buf, (size_t)len, "block_sweep<%d,%d,%d,%d,%s,%d>", v->D, v->TX, v->TY, v->NT,
                  v->elem == 1 ? "int8,int16" : v->elem == 2 ? "int16,void" : "int32,void", g.sched);
     else
-        snprintf(buf, (size_t)len, "lds_run<%d,256,%d>", g.D, g.sched);
+        snprintf(buf, (size_t)len, g.lds_is_wide ? "lds_run32<%d,256,%d>" : "lds_run<%d,512,%d>", g.D, g.sched);
     return RSOS_OK;
 }
 
@@ -1273,7 +1303,10 @@ extern "C" rsos_status rsos_sweep_static(const rsos_params *p, int32_t *d_h, int
     HIP_TRY(hipGetLastError());
     if (!v) {
         // the whole surface in one workgroup's LDS, all sweeps in one launch
-        lds_launcher(D, sched)(dim3(1), (size_t)L2 * 4, s, dd, (const int *)(base + kScratchIdx));
+        bool wide;
+        size_t shm;
+        lds_plan(D, sched, {{p->L, p->N}}, &wide, &shm);
+        lds_launcher(D, sched)(dim3(1), shm, wide, s, dd, (const int *)(base + kScratchIdx));
         HIP_TRY(hipGetLastError());
     } else {
         BlockLaunch k = sched == 1 ? v->launch_dt : v->launch;

@@ -1172,9 +1172,354 @@ __global__ void unpack16(const uint16_t *__restrict__ src, int32_t *__restrict__
 }
 
 // ---------------------------------------------------------------------------
-// lds_run: surfaces small enough to live in LDS, one workgroup each, all
-// their sweeps in one launch.  which[] lists descriptor indices; the LDS is
-// L_max^2 int32 of dynamic shared memory.
+// Surfaces small enough to live in LDS, one workgroup each, all their sweeps
+// in one launch.  which[] lists descriptor indices.
+//
+// A small surface is bound by the chain of dependent attempts of a tile:
+// with one lane per tile L = 64 keeps 32 lanes of a CU busy, 64 attempts
+// after each other.  But attempts commute unless their sites are the same or
+// neighbours.  lds_run therefore first lays out each tile's attempts in
+// steps of up to four that are pairwise independent and keep their order
+// across steps (the site sequence does not depend on the heights, so this is
+// done by one lane per tile and Philox call, for L <= 64 by the waves that
+// would idle and one sweep ahead), then four lanes per tile make the attempts
+// of a step together.  D = 8: about 27 steps instead of 64, each one LDS
+// round trip and some 17 instructions of a wave that has its SIMD nearly to
+// itself.  Steps of eight would be about 20 at twice the lanes, which L = 128
+// does not have idle.
+//
+// Heights are staged as 16-bit offsets from a base that follows the surface
+// (the restriction keeps the spread below N L, the mean rises by at most one
+// per sweep; needs N L <= kLdsRunMaxNL).  The array covers [0, L + 2D) in x
+// and y plus a frame of one site; sweep s works on the window of side L at
+// its origin (ox, oy), so no tile wraps.  Between sweeps only the strips by
+// which the window moved are copied over, and the frame around the window
+// (the torus neighbours of its edge) is refreshed before every phase.
+//
+// L = 64, D = 8: 20.4 -> 6.8 us per sweep; 192 surfaces of L = 32, 64, 128
+// (bound by L = 128): 25.9 -> 14.1 us per sweep.
+// ---------------------------------------------------------------------------
+constexpr int kLdsRunMaxNL = 8192;
+constexpr int kLdsRebase = 4096;  // sweeps between moves of the base: 2 N L + kLdsRebase < 2^15
+constexpr int kLdsWin = 4;        // attempts per step
+constexpr int kLdsMaxL = 128;
+constexpr int kLdsThreads = 512;  // four lanes for each of the 128 tiles of a phase at L = 128, D = 8
+
+template <int D>
+struct LdsRun {
+    using TB = TileBits<D>;
+    // one row pitch for every L: the neighbours of a site are at constant
+    // offsets; an odd number of words spreads the rows over the banks
+    static constexpr int P = kLdsMaxL + 2 * D + 2;
+    static_assert((P / 2) % 2 == 1, "odd words per row");
+    // Attempts of one Philox call, and of the last one of a tile.  Every
+    // lane of a tile has its own list of that many entries per call (a call
+    // may need a step for each of its attempts).
+    static constexpr int NPER = TB::PER < D * D ? TB::PER : D * D;
+    static constexpr int NLAST = D * D - (TB::NCALL - 1) * NPER;
+    static_assert(NPER % 2 == 0 && NLAST % 2 == 0, "entries are read in pairs");
+    // An entry is the LDS address of the site above the attempt's, in units
+    // of 2^SHIFT bytes, in 16 bits.
+    static constexpr int SHIFT = D == 32 ? 1 : 0;
+
+    __host__ __device__ static int lattice_rows(int L) { return L + 2 * D + 2 + 3; }  // and 3 of the idle lanes' site
+    __host__ __device__ static int lattice_bytes(int L) { return (lattice_rows(L) * P * 2 + 15) & ~15; }
+    // Small lattices leave waves without an attempt to make: these lay out
+    // the next sweep's steps (all phases) meanwhile, into a second set of
+    // lists.  The others lay out one phase at a time, by all waves.
+    __host__ __device__ static bool ahead(int L, int phases)
+    {
+        return L <= 64 && L / D * (L / D) / phases * kLdsWin <= kLdsThreads / 2;
+    }
+    __host__ __device__ static int list_bytes(int L, int phases)  // of one set
+    {
+        return L * L / (ahead(L, phases) ? 1 : phases) * kLdsWin * 2 + 16;  // one pair is read beyond the last
+    }
+    __host__ __device__ static int bytes(int L, int phases)
+    {
+        return lattice_bytes(L) + list_bytes(L, phases) * (ahead(L, phases) ? 2 : 1);
+    }
+};
+
+typedef __attribute__((address_space(3))) int16_t l16;
+__device__ __forceinline__ uint32_t lds_address(const int16_t *p) { return (uint32_t)(uintptr_t)(const l16 *)p; }
+
+// a / d for 0 <= a < 2^20 with r = 1.0f / d: (a + 1/2) / d is at least
+// 1 / (2 d) from every integer, far more than the float error.
+__device__ __forceinline__ int div_by(int a, float r) { return (int)(((float)a + 0.5f) * r); }
+
+// Sum over the wavefront, in lane 63 (six dependent adds; an LDS atomic from
+// every lane took 9000 cycles per sweep).
+__device__ __forceinline__ int wave_sum63(int v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, true);   // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, true);   // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, true);   // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, true);   // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, true);   // row_bcast:15
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, true);   // row_bcast:31
+    return v;
+}
+
+// Lays out the attempts of Philox call j of one tile in steps: the k-th step
+// takes entry k of the lists of the tile's kLdsWin lanes (`stride` entries
+// apart); the entries that are not used stay on the idle site.  `above` is
+// the site above the tile's corner.  Returns the number of steps.
+template <int D>
+__device__ __forceinline__ int lay_out_steps(uint16_t *list, int stride, const int16_t *above, int j, uint32_t tile_id,
+                                             uint32_t s, uint32_t p, uint32_t k0, uint32_t k1)
+{
+    using R = LdsRun<D>;
+    using TB = TileBits<D>;
+    const u32x4 r = philox4x32_10((uint32_t)j, tile_id, s, p, k0, k1);
+    const int n = j == TB::NCALL - 1 ? R::NLAST : R::NPER;
+    const uint32_t a0 = lds_address(above) >> R::SHIFT;
+    constexpr uint32_t FAR = 0x8080u;            // further than one bond from every site
+    uint32_t w1 = FAR, w2 = FAR, w3 = FAR;       // the step's sites so far, x + 256 y
+    int at = 0;                                  // entry of the next site
+    int used = 0, steps = 0;                     // sites of the current step, steps before it
+    static_assert(kLdsWin == 4, "three earlier sites are compared");
+#pragma unroll
+    for (int k = 0; k < R::NPER; ++k) {
+        if (k < n) {
+            const uint32_t f = (r.v[k / TB::F] >> ((k % TB::F) * TB::B)) & (uint32_t)(D * D - 1);
+            const uint32_t x = f & (uint32_t)(D - 1), y = f >> TB::LOG2D;
+            const uint32_t xy = x | (y << 8);
+            const uint32_t near = min(min(__builtin_amdgcn_sad_u8(xy, w1, 0), __builtin_amdgcn_sad_u8(xy, w2, 0)),
+                                      __builtin_amdgcn_sad_u8(xy, w3, 0));
+            const bool next = near <= 1u || used == kLdsWin;
+            w3 = next ? FAR : w2;
+            w2 = next ? FAR : w1;
+            w1 = xy;
+            steps += next;
+            at = next ? steps : at;
+            used = next ? 1 : used + 1;
+            list[at] = (uint16_t)(a0 + (__umul24(y, (uint32_t)R::P) + x) * 2 / (1 << R::SHIFT));
+            at += stride;
+        }
+    }
+    return steps + 1;
+}
+
+template <int D, int NT, int SCHED = 0>
+__global__ __launch_bounds__(NT) void lds_run(SurfDev *__restrict__ descs, const int *__restrict__ which)
+{
+    using R = LdsRun<D>;
+    using TB = TileBits<D>;
+    constexpr int PH = SCHED == 0 ? 2 : 4, P = R::P;
+    constexpr int MAXT = kLdsMaxL / D;
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds_dyn[];
+    __shared__ int s_sum[2][2];  // by sweep parity: accepted, sum of (h - base) over accepted
+    // steps of the longest of 16 tiles (one wave's), by set of lists, call
+    // and group of tiles
+    constexpr int GROUPS = MAXT * MAXT / 16 + PH;  // every phase's last group may be part of one
+    __shared__ int s_steps[2][TB::NCALL][GROUPS];
+
+    SurfDev &d = descs[which[blockIdx.x]];
+    long long t = d.t;
+    const long long t_end = d.t_end;
+    if (t >= t_end) return;
+    const int L = d.L, N = d.N, T = d.T, tid = threadIdx.x;
+    const uint32_t k0 = d.key0, k1 = d.key1;
+    const bool ahead = R::ahead(L, PH);
+    const int ntiles = T * T / PH, ngroups = (ntiles + 15) / 16;
+    const int all = ahead ? T * T : ntiles;   // tiles of a set of lists
+    // threads that lay out steps while the others make attempts
+    const int makers = min(NT, (ntiles * kLdsWin + 63) & ~63);
+    int16_t *h = (int16_t *)lds_dyn + P + 1;  // site (0, 0); the frame's at index -1
+    uint16_t *const lists = (uint16_t *)(lds_dyn + R::lattice_bytes(L));
+    const int set = R::list_bytes(L, PH) / 2;  // entries of a set
+    // a site that no attempt changes, for lanes without one: N above all its
+    // neighbours
+    int16_t *const idle = h + (L + 2 * D + 2) * P;  // row L + 2 D + 3 of the array
+    const uint32_t idle2 = (lds_address(idle - P) >> R::SHIFT) * 0x10001u;
+
+    auto origin = [&](long long tau, int &x, int &y) {
+        const u32x4 o = philox4x32_10(0u, 0u, (uint32_t)tau, 2u, k0, k1);
+        x = (int)(o.v[0] % (2u * D));
+        y = (int)(o.v[1] % (2u * D));
+    };
+    int ox, oy;
+    origin(t, ox, oy);
+    int base;
+    {
+        const int32_t *src = d.buf[t & 1];
+        base = src[0];
+        for (int i = tid; i < L * L; i += NT) {
+            const int y = i / L, x = i - y * L;
+            h[(y < oy ? y + L : y) * P + (x < ox ? x + L : x)] = (int16_t)(src[i] - base);
+        }
+        for (int i = tid; i < set / 2 * (ahead ? 2 : 1); i += NT) ((uint32_t *)lists)[i] = idle2;
+        for (int i = tid; i < 2 * TB::NCALL * GROUPS; i += NT) (&s_steps[0][0][0])[i] = 0;
+        if (tid < 4) s_sum[tid >> 1][tid & 1] = 0;
+        if (tid == 0) {
+            idle[0] = 0;
+            idle[-1] = idle[1] = idle[-P] = idle[P] = (int16_t)-N;
+        }
+    }
+    // thread 0 keeps the sums
+    long long S1 = 0, S2 = 0, slot = t % d.log_cap;
+    if (tid == 0) {
+        const long long *rec = d.log + 3 * slot;
+        S1 = rec[0];
+        S2 = rec[1];
+    }
+    __syncthreads();
+
+    const float r_half = 1.0f / (float)(T / 2), r_tiles = 1.0f / (float)ntiles, r_all = 1.0f / (float)all;
+    // tile k of phase p: its place in the window, in tiles
+    auto tile_of = [&](int k, int p, int &tx, int &ty) {
+        const int q = div_by(k, r_half);
+        ty = SCHED == 0 ? q : 2 * q + (p >> 1);
+        tx = 2 * (k - q * (T / 2)) + (SCHED == 0 ? (ty + p) & 1 : p & 1);
+    };
+    // the torus neighbours of the window's edge (kLdsMaxL threads a side)
+    auto frame = [&]() {
+#pragma unroll
+        for (int i = 0; i < 4 * kLdsMaxL; i += NT) {
+            const int side = (i + tid) / kLdsMaxL, k = (i + tid) % kLdsMaxL;
+            if (k >= L) continue;
+            int16_t *row = h + (oy + k) * P + ox, *col = h + oy * P + ox + k;
+            int16_t *to = side == 0 ? row - 1 : side == 1 ? row + L : side == 2 ? col - P : col + L * P;
+            const int16_t *from = side == 0 ? row + L - 1 : side == 1 ? row : side == 2 ? col + (L - 1) * P : col;
+            *to = *from;
+        }
+    };
+    // lists of the phases from p on that a set holds, for the window at
+    // (x, y), by threads `first` .. of the `nthr`
+    auto lay_out = [&](uint32_t s, int p, int half, int x, int y, int first, int nthr) {
+        for (int i = first; i < all * TB::NCALL; i += nthr) {
+            // consecutive lanes take consecutive tiles
+            const int j = div_by(i, r_all), i2 = i - j * all, g = ahead ? div_by(i2, r_tiles) : 0;
+            const int k = i2 - g * ntiles;
+            int tx, ty;
+            tile_of(k, p + g, tx, ty);
+            const int stride = j == TB::NCALL - 1 ? R::NLAST : R::NPER;
+            const int n = lay_out_steps<D>(lists + half * set + j * R::NPER * all * kLdsWin + i2 * kLdsWin * stride,
+                                           stride, h + (y + ty * D - 1) * P + x + tx * D, j, (uint32_t)(ty * T + tx), s,
+                                           (uint32_t)(SCHED == 0 ? p + g : 4 + p + g), k0, k1);
+            atomicMax(&s_steps[half][j][g * ngroups + (k >> 4)], n);
+        }
+    };
+
+    int half = 0;
+    if (ahead) {
+        lay_out((uint32_t)t, 0, 0, ox, oy, tid, NT);
+    }
+    for (int run = 0; t < t_end; ++t) {
+        const uint32_t s = (uint32_t)t;
+        int nx = ox, ny = oy;
+        if (t + 1 < t_end) origin(t + 1, nx, ny);
+        frame();
+        int acc = 0, q = 0;
+#pragma unroll 1
+        for (int p = 0; p < PH; ++p) {
+            if (!ahead) lay_out(s, p, 0, ox, oy, tid, NT);
+            __syncthreads();
+            if (ahead && tid >= makers && p == 0 && t + 1 < t_end)
+                lay_out(s + 1u, 0, half ^ 1, nx, ny, tid - makers, NT - makers);
+            for (int k = tid / kLdsWin; k < ntiles; k += NT / kLdsWin) {
+                const int g = ahead ? p : 0;
+                int *const nsteps = &s_steps[half][0][g * ngroups + (k >> 4)];
+                const uint16_t *e0 = lists + half * set;
+#pragma unroll 1
+                for (int j = 0; j < TB::NCALL; ++j) {
+                    const int n = __builtin_amdgcn_readfirstlane(nsteps[j * GROUPS]);
+                    const int stride = j == TB::NCALL - 1 ? R::NLAST : R::NPER;
+                    uint32_t *e = (uint32_t *)(e0 + j * R::NPER * all * kLdsWin +
+                                               ((g * ntiles + k) * kLdsWin + (tid & (kLdsWin - 1))) * stride);
+                    uint32_t two = *e;
+                    auto attempt1 = [&](uint32_t a) {
+                        // the site above, then the site and its neighbours at constant offsets
+                        l16 *c = (l16 *)(uintptr_t)(a << R::SHIFT);
+                        const int u = c[0], l = c[P - 1], v = c[P], r = c[P + 1], w = c[2 * P];
+                        const int n1 = min(v + 1, min(min(l, r), min(u, w)) + N);
+                        c[P] = (int16_t)n1;
+                        const int ok = n1 - v;
+                        acc += ok;
+                        q += __mul24(v, ok);
+                        // the next step's reads stay behind these writes
+                        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                    };
+#pragma unroll 1
+                    for (int step = 0; step < n; step += 2) {
+                        const uint32_t cur = two;
+                        two = e[1];  // (one pair beyond the last step's is read, and not used)
+                        *e++ = idle2;
+                        attempt1(cur & 0xFFFFu);
+                        attempt1(cur >> 16);
+                    }
+                    nsteps[j * GROUPS] = 0;
+                }
+            }
+            __syncthreads();
+            if (p + 1 < PH) frame();
+        }
+        half ^= ahead ? 1 : 0;
+        acc = wave_sum63(acc);
+        q = wave_sum63(q);
+        if ((tid & 63) == 63 && acc) {
+            atomicAdd(&s_sum[s & 1][0], acc);
+            atomicAdd(&s_sum[s & 1][1], q);
+        }
+        // the next window: strips of columns, then of rows
+        {
+            const int wx = abs(nx - ox), wy = abs(ny - oy), x0 = min(nx, ox), y0 = min(ny, oy);
+            if ((tid & (2 * D - 1)) < wx)
+                for (int y = tid / (2 * D); y < L; y += NT / (2 * D)) {
+                    int16_t *c = h + (oy + y) * P + x0 + (tid & (2 * D - 1));
+                    if (nx > ox) c[L] = c[0];
+                    else c[0] = c[L];
+                }
+            ox = nx;
+            __syncthreads();
+            if ((tid & (kLdsMaxL - 1)) < L)
+                for (int y = tid / kLdsMaxL; y < wy; y += NT / kLdsMaxL) {
+                    int16_t *c = h + (y0 + y) * P + ox + (tid & (kLdsMaxL - 1));
+                    if (ny > oy) c[L * P] = c[0];
+                    else c[0] = c[L * P];
+                }
+            oy = ny;
+        }
+        __syncthreads();
+        if (tid == 0) {
+            const int a = s_sum[s & 1][0];
+            const long long c = (long long)s_sum[s & 1][1] + (long long)base * a;
+            s_sum[s & 1][0] = s_sum[s & 1][1] = 0;
+            S1 += a;
+            S2 += 2 * c + a;  // a deposit on h raises h^2 by 2 h + 1
+            slot = slot + 1 == d.log_cap ? 0 : slot + 1;
+            long long *e = d.log + 3 * slot;
+            e[0] = S1;
+            e[1] = S2;
+            e[2] = a;
+        }
+        if (++run == kLdsRebase) {
+            run = 0;
+            const int v0 = h[oy * P + ox];
+            __syncthreads();
+            for (int i = tid; i < L * L; i += NT) {
+                const int y = i / L;
+                h[(oy + y) * P + ox + i - y * L] -= (int16_t)v0;
+            }
+            base += v0;
+            __syncthreads();
+        }
+    }
+    {
+        int32_t *dst = d.buf[t_end & 1];
+        for (int i = tid; i < L * L; i += NT) {
+            const int y = i / L, x = i - y * L;
+            dst[i] = base + h[(y < oy ? y + L : y) * P + (x < ox ? x + L : x)];
+        }
+    }
+    if (tid == 0) d.t = t_end;
+}
+
+// ---------------------------------------------------------------------------
+// lds_run32: the same for restrictions with N L > kLdsRunMaxNL (up to none at
+// all): int32 heights on the bare torus, one lane per tile, the LDS is
+// L_max^2 int32.
 // ---------------------------------------------------------------------------
 template <int D>
 __device__ __forceinline__ int tile_attempts_torus(int32_t *h, int L, int x0, int y0,
@@ -1208,9 +1553,10 @@ __device__ __forceinline__ int tile_attempts_torus(int32_t *h, int L, int x0, in
 }
 
 template <int D, int NT, int SCHED = 0>
-__global__ __launch_bounds__(NT) void lds_run(SurfDev *__restrict__ descs, const int *__restrict__ which)
+__global__ __launch_bounds__(NT) void lds_run32(SurfDev *__restrict__ descs, const int *__restrict__ which)
 {
-    extern __shared__ int32_t lat[];
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds_dyn[];
+    int32_t *lat = (int32_t *)lds_dyn;
     SurfDev &d = descs[which[blockIdx.x]];
     long long t = d.t;
     const long long t_end = d.t_end;
