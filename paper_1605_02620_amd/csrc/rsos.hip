@@ -47,6 +47,7 @@ namespace {
 constexpr int kLdsMaxBytes = 64 * 1024;  // surfaces of at most this many bytes of int32 run whole in LDS
 constexpr int kGraphSweeps = 32;
 constexpr long long kNoEnd = 0x7FFFFFFFFFFFFFFFll;  // t_end of a surface with no bound
+constexpr int kCUs = 256;           // of an MI355X
 constexpr int kPsGrid = 2048;       // workgroups of the power-sum reduction
 constexpr size_t kStagingBytes = 4096;      // least size of a pinned staging buffer
 constexpr long long kReadRecords = 1 << 15; // most log records copied at once (768 KiB pinned)
@@ -98,6 +99,7 @@ struct Variant {
     BlockLaunch launch;       // int32 storage (elem 1: int16 sub-blocks where int8 does not fit)
     BlockLaunch launch16;     // 16-bit storage, uint8 staging with int16 sub-blocks (nullptr: not offered)
     BlockLaunch launch_dt;    // double-tiling schedule, int32 storage (nullptr: not offered)
+    bool steps = false;       // attempts in steps: for launches that leave most lanes idle
 };
 
 #define P16(D, TX, TY, NT) launch_block16<D, TX, TY, NT>
@@ -114,6 +116,8 @@ struct Variant {
      dt_launcher<D, TX, TY, NT, int16_t, void>()}
 #define V32(D, TX, TY, NT) \
     {D, TX, TY, NT, 4, launch_block<D, TX, TY, NT, int32_t, void, 0>, nullptr, dt_launcher<D, TX, TY, NT, int32_t, void>()}
+// Attempts in steps (int16 staging): checkerboard on int32 storage only.
+#define VS(D, TX, TY, NT) {D, TX, TY, NT, 2, launch_block<D, TX, TY, NT, int16_t, void, 2>, nullptr, nullptr, true}
 // In order of preference; without a tuned choice the first one that fits
 // every surface is used.
 // (V8N: the same int8 kernel without a 16-bit storage instance, where a
@@ -126,6 +130,7 @@ const Variant kVariants[] = {
     V32(8, 8, 8, 64), V32(8, 2, 2, 64), V8(8, 16, 16, 256), V8N(8, 16, 8, 128),
     V16P(16, 4, 4, 64), V32(16, 4, 4, 64), V32(16, 2, 2, 64), V8(16, 4, 4, 64), V8(16, 8, 8, 256),
     V8(32, 2, 2, 64), V32(32, 2, 2, 64),
+    VS(8, 8, 8, 256), VS(8, 16, 8, 512), VS(16, 4, 4, 384),
 };
 #undef P16
 #undef V8
@@ -133,6 +138,7 @@ const Variant kVariants[] = {
 #undef V16
 #undef V16P
 #undef V32
+#undef VS
 
 bool variant_fits(const Variant &v, int L, int N, bool packed, bool dt = false)
 {
@@ -173,10 +179,26 @@ const Variant *pick_variant(int D, const std::vector<std::pair<int, int>> &LN, b
                             bool dt = false)
 {
     const char *force = getenv("RSOS_VARIANT");
+    // Attempts in steps where a whole sweep is at most one such workgroup
+    // per CU: L = 256 18.2 -> 14.0 us per sweep, L = 1024 20.6 -> 16.8,
+    // L = 1360 20.6 -> 18.4 (16 x 8 blocks), D = 16, L = 1024: 54.8 -> 29.0.
+    // With more blocks the lists cost more than the idle lanes: 64 surfaces
+    // of L = 256, four 8 x 8 blocks per CU, 21.1 -> 31.3.
+    if (!force && !packed && !dt)
+        for (const Variant &v : kVariants) {
+            if (v.D != D || !v.steps) continue;
+            bool ok = true;
+            long long blocks = 0;
+            for (auto &ln : LN) {
+                ok = ok && variant_fits(v, ln.first, ln.second, false, false);
+                blocks += (long long)blocks_along(ln.first / D, v.TX) * blocks_along(ln.first / D, v.TY);
+            }
+            if (ok && blocks <= kCUs) return &v;
+        }
     const Variant *least = nullptr;
     double least_staged = 0;
     for (const Variant &v : kVariants) {
-        if (v.D != D) continue;
+        if (v.D != D || (v.steps && !force)) continue;
         if (force) {
             char want[48];
             snprintf(want, sizeof want, "%dx%dx%dx%d", v.TX, v.TY, v.NT, packed ? 16 : v.elem);
@@ -516,7 +538,10 @@ struct SurfaceGroup {
         rsos_status st = staging.ensure(sizeof(SurfDev) * n);
         if (st != RSOS_OK) return st;
         SurfDev *h = (SurfDev *)staging.host;
-        for (int k = 0; k < n; ++k) h[k] = host[rows[k]];
+        for (int k = 0; k < n; ++k) {
+            h[k] = host[rows[k]];
+            h[k].slot = h[k].t % h[k].log_cap;
+        }
         return staging.copy_to(d_desc, sizeof(SurfDev) * n, stream);
     }
 
@@ -1236,7 +1261,7 @@ __global__ void static_setup(SurfDev d, unsigned char *base, long long s1, long 
         *(int *)(base + kScratchIdx) = 0;
         const long long L2 = (long long)d.L * d.L;
         acc[rsosk::kMeanWord] = s1 / L2;
-        long long *rec = d.log + 3 * (d.t % d.log_cap);
+        long long *rec = d.log + 3 * d.slot;
         rec[0] = s1;
         rec[1] = s2;
         rec[2] = 0;
@@ -1283,6 +1308,7 @@ extern "C" rsos_status rsos_sweep_static(const rsos_params *p, int32_t *d_h, int
     d.acc = (long long *)(base + kScratchAcc);
     d.log_cap = kStaticLogCap;
     d.t = t0;
+    d.slot = t0 % kStaticLogCap;
     d.t_end = t0 + n_mcs;
     d.key0 = (uint32_t)(p->seed & 0xFFFFFFFFu);
     d.key1 = (uint32_t)(p->seed >> 32);

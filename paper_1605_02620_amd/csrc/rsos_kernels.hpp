@@ -76,15 +76,15 @@ __host__ __device__ __forceinline__ u32x4 philox4x32_10(uint32_t c0, uint32_t c1
 // host writes it at setup and sets t_end before a run; the sweep's last
 // block (or lds_run) advances t.
 // ---------------------------------------------------------------------------
-constexpr int kAccSlots = 64;  // per-surface spread of the (S1, S2, A) atomics
-// Per-surface accumulator area: 3 * kAccSlots words of increments, then
-// word kMeanWord = floor(S1 / L^2) of the current time (kept by the sweep's
-// last block; the 16-bit storage mode recovers true heights from it, every
-// block reads it) and, in a 128-byte line of its own so that the blocks'
+constexpr int kAccSlots = 64;  // per-surface spread of the (S1, S2) atomics
+// Per-surface accumulator area: 2 * kAccSlots words of increments, then
+// word kMeanWord = floor(S1 / L^2) of the current time (16-bit storage only,
+// which recovers true heights from it: kept by the sweep's last block, read
+// by every block) and, in a 128-byte line of its own so that the blocks'
 // atomic additions to it do not stall those reads, word kDoneWord, the
 // blocks of the running sweep that have committed.  All words but
 // kMeanWord are zero between sweeps.  Areas are 128-byte aligned.
-constexpr int kMeanWord = 3 * kAccSlots;
+constexpr int kMeanWord = 2 * kAccSlots;
 constexpr int kDoneWord = kMeanWord + 16;
 constexpr int kAccWords = kDoneWord + 16;
 
@@ -120,6 +120,7 @@ struct SurfDev {
     long long *acc;       // kAccWords int64: accumulators (zero between sweeps), mean floor
     long long log_cap;
     long long t;          // sweeps done
+    long long slot;       // t % log_cap
     long long t_end;      // run while t < t_end
     uint32_t key0, key1;  // Philox key = seed
     int L, N, T;          // T = L / D
@@ -460,7 +461,211 @@ __device__ __forceinline__ void block_phases_dt(E *lds, int off, BlockPos bp, in
     }
 }
 
-// Schedule selector: 0 = tile checkerboard, 1 = double tiling.
+// ---------------------------------------------------------------------------
+// Attempts in steps.  Attempts commute unless their sites are the same or
+// neighbours, so where too few tiles are at work to fill the lanes, a tile's
+// attempts are laid out in steps of up to kLdsWin pairwise independent ones
+// that keep their order across steps (one lane per tile and Philox call; the
+// site sequence does not depend on the heights), and kLdsWin lanes of a tile
+// make the attempts of a step together: for D = 8 about 27 steps, each one
+// LDS round trip, instead of 64.  Used on int16 staging.
+// ---------------------------------------------------------------------------
+constexpr int kLdsWin = 4;        // attempts per step
+
+// Attempts of one Philox call, and of the last one of a tile.  Every lane of
+// a tile has its own list of that many entries per call (a call may need a
+// step for each of its attempts); an entry is the LDS address of the site
+// above the attempt's (in units of 2^SHIFT bytes, in 16 bits).
+template <int D>
+struct StepList {
+    using TB = TileBits<D>;
+    static constexpr int NPER = TB::PER < D * D ? TB::PER : D * D;
+    static constexpr int NLAST = D * D - (TB::NCALL - 1) * NPER;
+    static_assert(NPER % 2 == 0 && NLAST % 2 == 0, "entries are read in pairs");
+};
+
+typedef __attribute__((address_space(3))) int16_t l16;
+__device__ __forceinline__ uint32_t lds_address(const int16_t *p) { return (uint32_t)(uintptr_t)(const l16 *)p; }
+
+// a / d for 0 <= a < 2^20 with r = 1.0f / d: (a + 1/2) / d is at least
+// 1 / (2 d) from every integer, far more than the float error.
+__device__ __forceinline__ int div_by(int a, float r) { return (int)(((float)a + 0.5f) * r); }
+
+// Sum over the wavefront, in lane 63 (six dependent adds; an LDS atomic from
+// every lane took 9000 cycles per sweep).
+__device__ __forceinline__ int wave_sum63(int v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, true);   // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, true);   // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, true);   // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, true);   // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, true);   // row_bcast:15
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, true);   // row_bcast:31
+    return v;
+}
+
+// Lays out the attempts of Philox call j of one tile in steps: the k-th step
+// takes entry k of the lists of the tile's kLdsWin lanes (`stride` entries
+// apart, 16-byte aligned); the entries that are not used name the idle site
+// (idle2: its entry twice).  `above` is the site above the tile's corner.
+// Returns the number of steps.
+template <int D, int P, int SHIFT>
+__device__ __forceinline__ int lay_out_steps(uint16_t *list, int stride, const int16_t *above, uint32_t idle2, int j,
+                                             uint32_t tile_id, uint32_t s, uint32_t p, uint32_t k0, uint32_t k1)
+{
+    using R = StepList<D>;
+    using TB = TileBits<D>;
+    const u32x4 r = philox4x32_10((uint32_t)j, tile_id, s, p, k0, k1);
+    const int n = j == TB::NCALL - 1 ? R::NLAST : R::NPER;
+#pragma unroll
+    for (int i = 0; i < R::NPER / 2; ++i)
+        if (i < n / 2) ((uint4 *)list)[i] = make_uint4(idle2, idle2, idle2, idle2);
+    const uint32_t a0 = lds_address(above) >> SHIFT;
+    constexpr uint32_t FAR = 0x8080u;            // further than one bond from every site
+    uint32_t w1 = FAR, w2 = FAR, w3 = FAR;       // the step's sites so far, x + 256 y
+    int at = 0;                                  // entry of the next site
+    int used = 0, steps = 0;                     // sites of the current step, steps before it
+    static_assert(kLdsWin == 4, "three earlier sites are compared");
+#pragma unroll
+    for (int k = 0; k < R::NPER; ++k) {
+        if (k < n) {
+            const uint32_t f = (r.v[k / TB::F] >> ((k % TB::F) * TB::B)) & (uint32_t)(D * D - 1);
+            const uint32_t x = f & (uint32_t)(D - 1), y = f >> TB::LOG2D;
+            const uint32_t xy = x | (y << 8);
+            const uint32_t near = min(min(__builtin_amdgcn_sad_u8(xy, w1, 0), __builtin_amdgcn_sad_u8(xy, w2, 0)),
+                                      __builtin_amdgcn_sad_u8(xy, w3, 0));
+            const bool next = near <= 1u || used == kLdsWin;
+            w3 = next ? FAR : w2;
+            w2 = next ? FAR : w1;
+            w1 = xy;
+            steps += next;
+            at = next ? steps : at;
+            used = next ? 1 : used + 1;
+            list[at] = (uint16_t)(a0 + (__umul24(y, (uint32_t)P) + x) * 2 / (1 << SHIFT));
+            at += stride;
+        }
+    }
+    return steps + 1;
+}
+
+// The attempts of one lane's list of a call: n steps (rounded up to pairs)
+// on staging with row pitch P.
+template <int P, int SHIFT>
+__device__ __forceinline__ void make_steps(const uint32_t *e, int n, int N, int &acc, int &q)
+{
+    auto attempt1 = [&](uint32_t a) {
+        // the site above, then the site and its neighbours at constant offsets
+        l16 *c = (l16 *)(uintptr_t)(a << SHIFT);
+        const int u = c[0], l = c[P - 1], v = c[P], r = c[P + 1], w = c[2 * P];
+        // a deposit is accepted iff v + 1 <= m + N, and v <= m + N always
+        const int n1 = min(v + 1, min(min(l, r), min(u, w)) + N);
+        c[P] = (int16_t)n1;
+        const int ok = n1 - v;
+        acc += ok;
+        q += __mul24(v, ok);
+        // the next step's reads stay behind these writes
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    };
+    uint32_t two = *e;
+#pragma unroll 1
+    for (int step = 0; step < n; step += 2) {
+        const uint32_t cur = two;
+        two = *++e;  // (one pair beyond the last step's is read, and not used)
+        attempt1(cur & 0xFFFFu);
+        attempt1(cur >> 16);
+    }
+}
+
+// Both phases of block_phases on int16 staging, in steps.  lay_out_block
+// fills the lists (it reads no height, so it runs while the region's loads
+// are on their way), block_phases_steps makes the attempts.
+template <int D, int TX, int TY, int NT, int RWL, int RH>
+struct BlockSteps {
+    using TB = TileBits<D>;
+    using R = StepList<D>;
+    static constexpr int RING = D + 1, HALF = TX * TY / 2, P0 = HALF + TX + TY, ALL = P0 + HALF;
+    static constexpr int G0 = (P0 + 15) / 16, GROUPS = G0 + (HALF + 15) / 16;
+    // after the region: the idle site with its neighbours, the lists, the
+    // longest number of steps of each 16 tiles by call
+    static constexpr int IDLE = (RWL * RH + 7) & ~7;                // element
+    static constexpr int LISTS = (IDLE + 2 * RWL + 2 + 7) & ~7;     // element
+    static constexpr int STEPS = LISTS + ALL * D * D * kLdsWin + 8; // element (a pair is read beyond the lists)
+    static constexpr int BYTES = 2 * STEPS + 4 * TB::NCALL * GROUPS;
+
+    // tile k of the list: phase 0's (block_phases' order), then phase 1's
+    static __device__ __forceinline__ void tile(int k, int &ltx, int &lty)
+    {
+        const int p = k >= P0;
+        const int i = p ? k - P0 : k;
+        lty = i / (TX / 2);
+        ltx = 2 * (i % (TX / 2)) + ((lty + p) & 1);
+        if (!p && i >= HALF) {
+            const int g = i - HALF;
+            if (g < TX / 2) { lty = -1; ltx = 2 * g + 1; }
+            else if (g < TX) { lty = TY; ltx = 2 * (g - TX / 2); }
+            else if (g < TX + TY / 2) { ltx = -1; lty = 2 * (g - TX) + 1; }
+            else { ltx = TX; lty = 2 * (g - TX - TY / 2); }
+        }
+    }
+    static __device__ __forceinline__ uint32_t idle2(int16_t *lds) { return lds_address(lds + IDLE + 1) * 0x10001u; }
+
+    // before the workgroup's first barrier
+    static __device__ __forceinline__ void clear(int16_t *lds, int N)
+    {
+        int *steps = (int *)(lds + STEPS);
+        for (int i = threadIdx.x; i < TB::NCALL * GROUPS; i += NT) steps[i] = 0;
+        if (threadIdx.x == 0) {
+            // N above its neighbours: never changes
+            int16_t *c = lds + IDLE + 1 + RWL;
+            c[0] = 0;
+            c[-1] = c[1] = c[-RWL] = c[RWL] = (int16_t)-N;
+        }
+    }
+    static __device__ __forceinline__ void lay_out(int16_t *lds, int off, BlockPos bp, int T, uint32_t s, uint32_t k0,
+                                                   uint32_t k1)
+    {
+        int *steps = (int *)(lds + STEPS);
+        for (int i = threadIdx.x; i < ALL * TB::NCALL; i += NT) {
+            const int j = i / ALL, k = i - j * ALL;  // consecutive lanes take consecutive tiles
+            int ltx, lty;
+            tile(k, ltx, lty);
+            int gtx = bp.tx + ltx, gty = bp.ty + lty;
+            gtx = gtx < 0 ? gtx + T : (gtx >= T ? gtx - T : gtx);
+            gty = gty < 0 ? gty + T : (gty >= T ? gty - T : gty);
+            const int stride = j == TB::NCALL - 1 ? R::NLAST : R::NPER;
+            const int16_t *above = lds + (lty * D + RING - 1) * RWL + ltx * D + off;
+            const int n = lay_out_steps<D, RWL, 0>((uint16_t *)(lds + LISTS) + (j * R::NPER * ALL + k * stride) * kLdsWin,
+                                                   stride, above, idle2(lds), j, (uint32_t)(gty * T + gtx), s, k >= P0 ? 1u : 0u, k0, k1);
+            atomicMax(&steps[j * GROUPS + (k < P0 ? k / 16 : G0 + (k - P0) / 16)], n);
+        }
+    }
+    static __device__ __forceinline__ void phases(int16_t *lds, BlockPos bp, int N, int &acc, int &q)
+    {
+        const int *steps = (const int *)(lds + STEPS);
+#pragma unroll 1
+        for (int p = 0; p < 2; ++p) {
+            for (int i = threadIdx.x / kLdsWin; i < (p ? HALF : P0); i += NT / kLdsWin) {
+                const int k = p ? P0 + i : i;
+                int a = 0, qq = 0;
+#pragma unroll 1
+                for (int j = 0; j < TB::NCALL; ++j) {
+                    const int n = __builtin_amdgcn_readfirstlane(steps[j * GROUPS + (p ? G0 : 0) + i / 16]);
+                    const int stride = j == TB::NCALL - 1 ? R::NLAST : R::NPER;
+                    const uint16_t *e = (const uint16_t *)(lds + LISTS) + (j * R::NPER * ALL + k * stride) * kLdsWin +
+                                  (threadIdx.x & (kLdsWin - 1)) * stride;
+                    make_steps<RWL, 0>((const uint32_t *)e, n, N, a, qq);
+                }
+                int ltx, lty;
+                tile(k, ltx, lty);
+                if ((p || i < HALF) && bp.counts(ltx, lty)) { acc += a; q += qq; }
+            }
+            __syncthreads();
+        }
+    }
+};
+
+// Schedule selector: 0 = tile checkerboard, 1 = double tiling, 2 = checkerboard
+// in steps (int16 staging).
 template <int SCHED, int D, int TX, int TY, int NT, int RWL, typename E, typename Q>
 __device__ __forceinline__ void sweep_phases(E *lds, int off, BlockPos bp, int T, uint32_t s, int N,
                                              uint32_t k0, uint32_t k1, int &acc, Q &q)
@@ -473,67 +678,109 @@ __device__ __forceinline__ void sweep_phases(E *lds, int off, BlockPos bp, int T
 
 // ---------------------------------------------------------------------------
 // End of a sweep.  Every block adds its increments (A, sum(2h + 1) over its
-// accepted deposits, A) of S1, S2 and the accepted count to one of the
-// surface's 64 accumulator slots and counts itself in the surface's done
-// word; the block that completes the count folds the slots into the record
-// of time t + 1 (the record of t plus the increments), clears them, keeps
-// floor(S1 / L^2) and advances the surface's time.  So one launch is a
+// accepted deposits) of S1 and S2 to one of the surface's 64 accumulator
+// slots and counts itself in the surface's done word; the block that
+// completes the count folds the slots into the record of time t + 1 (the
+// record of t plus the increments), clears them, keeps floor(S1 / L^2) where
+// the storage needs it and advances the surface's time.  So one launch is a
 // whole sweep, and the sums are exact whatever order the blocks finish in.
 // All of it uses device-scope atomics without fences (an acquire or release
 // at device scope would write back or invalidate the XCD's whole L2 in
-// every block): a block counts itself only after its three slot additions
+// every block): a block counts itself only after its two slot additions
 // have been performed (it waits for them), and the last block reads the
 // slots with device-scope atomic loads.  Its plain stores (time, log
 // record, mean) are read by later launches only.
+//
+// Each of these steps is a round trip of the order of a microsecond, which
+// small lattices cannot hide: in the attempts-in-steps kernel only wave 0
+// takes them, while the others make their stores.  Reductions are DPP additions (a 64-bit shuffle
+// is two LDS permutes), and nothing divides: the log slot is kept in the
+// descriptor.
 // ---------------------------------------------------------------------------
 
+// Sum over the wavefront, in lane 63.
+template <int CTRL, int MASK>
+__device__ __forceinline__ long long dpp_add64(long long v)
+{
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTRL, MASK, 0xF, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)((unsigned long long)v >> 32), CTRL, MASK, 0xF, true);
+    return v + (long long)(((unsigned long long)hi << 32) | lo);
+}
+__device__ __forceinline__ long long wave_sum63_64(long long v)
+{
+    v = dpp_add64<0x111, 0xF>(v);  // row_shr 1, 2, 4, 8
+    v = dpp_add64<0x112, 0xF>(v);
+    v = dpp_add64<0x114, 0xF>(v);
+    v = dpp_add64<0x118, 0xF>(v);
+    v = dpp_add64<0x142, 0xA>(v);  // row_bcast:15 into rows 1 and 3
+    v = dpp_add64<0x143, 0xC>(v);  // row_bcast:31 into rows 2 and 3
+    return v;
+}
+
 // Wave 0 of the block that completed the count.
+template <bool MEAN>
 __device__ __forceinline__ void finish_sweep(SurfDev &d, long long t)
 {
     const int lane = threadIdx.x;  // < 64
-    gu64 *a = (gu64 *)(d.acc + 3 * lane);
+    const gi64 *prev = (const gi64 *)(d.log + 3 * d.slot);
+    const long long p1 = prev[0], p2 = prev[1];
+    gu64 *a = (gu64 *)(d.acc + 2 * lane);
     long long x = (long long)__hip_atomic_load(a + 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     long long y = (long long)__hip_atomic_load(a + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    long long z = (long long)__hip_atomic_load(a + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(a + 0, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(a + 1, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(a + 2, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    wave_reduce3(x, y, z);
-    if (lane == 0) {
-        const gi64 *prev = (const gi64 *)(d.log + 3 * (t % d.log_cap));
-        gi64 *e = (gi64 *)(d.log + 3 * ((t + 1) % d.log_cap));
-        const long long s1 = prev[0] + x, s2 = prev[1] + y;
-        e[0] = s1;
-        e[1] = s2;
-        e[2] = z;
-        *(gi64 *)(d.acc + kMeanWord) = s1 / ((long long)d.L * d.L);
+    x = wave_sum63_64(x);
+    y = wave_sum63_64(y);
+    if (lane == 63) {
+        const long long slot = d.slot + 1 == d.log_cap ? 0 : d.slot + 1;
+        gi64 *e = (gi64 *)(d.log + 3 * slot);
+        e[0] = p1 + x;
+        e[1] = p2 + y;
+        e[2] = x;
+        if constexpr (MEAN) *(gi64 *)(d.acc + kMeanWord) = (p1 + x) / ((long long)d.L * d.L);
         __hip_atomic_store((gu64 *)(d.acc + kDoneWord), 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         *(gi64 *)&d.t = t + 1;
+        *(gi64 *)&d.slot = slot;
     }
 }
 
 // a = this thread's accepted count, s2 = its share of the S2 increment.
-// Called by the whole workgroup once its sums are final (before its
-// stores: nothing here depends on them).
+// Called by the whole workgroup once its sums are final.  Returns, in
+// thread 0, the number of the surface's blocks counted before this one.
 template <int NT>
-__device__ __forceinline__ void commit_sweep(SurfDev &d, int b, long long a, long long s2, long long t)
+__device__ __forceinline__ unsigned long long commit_sweep(SurfDev &d, int b, long long a, long long s2)
 {
-    __shared__ int s_last;
-    long long unused = 0;
-    block_reduce3<NT>(a, s2, unused);
-    if (threadIdx.x == 0) {
-        gu64 *slot = (gu64 *)(d.acc + 3 * (b & (kAccSlots - 1)));
-        __hip_atomic_fetch_add(slot + 0, (unsigned long long)a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_fetch_add(slot + 1, (unsigned long long)s2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_fetch_add(slot + 2, (unsigned long long)a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        // the three additions are performed before the block is counted
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        const unsigned long long prev = __hip_atomic_fetch_add((gu64 *)(d.acc + kDoneWord), 1ull,
-                                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        s_last = prev + 1 == (unsigned long long)d.nblocks;
+    __shared__ long long red[2][NT / 64];
+    a = wave_sum63_64(a);
+    s2 = wave_sum63_64(s2);
+    if ((threadIdx.x & 63) == 63) {
+        red[0][threadIdx.x >> 6] = a;
+        red[1][threadIdx.x >> 6] = s2;
     }
     __syncthreads();
-    if (s_last && threadIdx.x < 64) finish_sweep(d, t);
+    unsigned long long before = 0;
+    if (threadIdx.x == 0) {
+        a = red[0][0];
+        s2 = red[1][0];
+        for (int i = 1; i < NT / 64; ++i) {
+            a += red[0][i];
+            s2 += red[1][i];
+        }
+        gu64 *slot = (gu64 *)(d.acc + 2 * (b & (kAccSlots - 1)));
+        __hip_atomic_fetch_add(slot + 0, (unsigned long long)a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_fetch_add(slot + 1, (unsigned long long)s2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        // the two additions are performed before the block is counted
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        before = __hip_atomic_fetch_add((gu64 *)(d.acc + kDoneWord), 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    return before;
+}
+
+// Whether this block completed the count (wave 0; false in the others).
+// Waits for the count, and for every store that wave 0 has made before.
+__device__ __forceinline__ bool is_last(const SurfDev &d, unsigned long long before)
+{
+    return threadIdx.x < 64 && __builtin_amdgcn_readfirstlane((int)(before + 1 == (unsigned long long)d.nblocks)) != 0;
 }
 
 // Workgroup -> global block.  Mode 1: the dispatcher hands consecutive
@@ -678,6 +925,8 @@ __device__ __forceinline__ bool region_sweep(E *lds, SurfDev &d, BlockPos bp, lo
     const int gxa = gx0 - cpad;  // LDS column c holds global column gxa + c (mod L)
     const int ref = (sizeof(E) <= 2) ? hin[(size_t)gy0 * L + gx0] : 0;
 
+    const int off = G::RING + cpad;  // LDS column of block column 0
+
     int vmin = 0x7FFFFFFF, vmax = -0x7FFFFFFF;  // range of the staged heights (int8 staging)
     // ---- load the region in aligned 16-byte chunks, consecutive threads on
     // consecutive chunks (rows run on into the next), U chunks in flight per
@@ -717,6 +966,8 @@ __device__ __forceinline__ bool region_sweep(E *lds, SurfDev &d, BlockPos bp, lo
 #pragma unroll
             for (int u = 0; u < U; ++u)
                 if (i0 + u * NT < NCH) v[u] = fetch(i0 + u * NT);
+            // (no height is read: the loads are on their way meanwhile)
+            if constexpr (SCHED == 2) BlockSteps<D, TX, TY, NT, PP, G::RH>::lay_out(lds, off, bp, T, s, k0, k1);
 #pragma unroll
             for (int u = 0; u < U; ++u)
                 if (i0 + u * NT < NCH) stage(i0 + u * NT, v[u]);
@@ -732,16 +983,24 @@ __device__ __forceinline__ bool region_sweep(E *lds, SurfDev &d, BlockPos bp, lo
     __syncthreads();
     if (checked && *(volatile int *)s_bad) return false;  // uniform: the whole workgroup
 
-    const int off = G::RING + cpad;  // LDS column of block column 0
     int acc = 0;
     Q q = 0;
-    sweep_phases<SCHED, D, TX, TY, NT, PP, E, Q>(lds, off, bp, T, s, N, k0, k1, acc, q);
+    if constexpr (SCHED == 2) BlockSteps<D, TX, TY, NT, PP, G::RH>::phases(lds, bp, N, acc, q);
+    else sweep_phases<SCHED, D, TX, TY, NT, PP, E, Q>(lds, off, bp, T, s, N, k0, k1, acc, q);
     // a deposit on h raises S2 by 2h + 1; the staged value c stands for ref + c
     ca += acc;
     cs2 += 2ll * (long long)q + (long long)acc + 2ll * (long long)ref * acc;
-    // the block's sums are final: commit them before the stores, which
-    // other workgroups then overlap
-    if (commit_here) commit_sweep<NT>(d, b, ca, cs2, t);
+    // the block's sums are final: commit them before the stores
+    unsigned long long before = 0;
+    bool last = false;
+    if (commit_here) before = commit_sweep<NT>(d, b, ca, cs2);
+    // Many blocks in flight: better to wait for the count here than for the
+    // stores at the block's end, and to start the block's stores together
+    // (16 sweeps at L = 16384: 6.63 ms with waves 1..3 ahead, 6.50 ms so).
+    if (SCHED != 2 && commit_here) {
+        last = is_last(d, before);
+        __syncthreads();
+    }
 
     // ---- store the block: aligned 16-byte chunks (LDS and global columns
     // share their alignment), masked single stores in the partial chunks
@@ -807,6 +1066,8 @@ __device__ __forceinline__ bool region_sweep(E *lds, SurfDev &d, BlockPos bp, lo
             }
         }
     }
+    if (SCHED == 2 && commit_here) last = is_last(d, before);
+    if (last) finish_sweep<false>(d, t);
     return true;
 }
 
@@ -839,7 +1100,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(
                                                   const int *__restrict__ owner, int xmode, int xnbx)
 {
     using W = WideSplit<D, TX, TY, NT, 4, (int)sizeof(E), WideSize<EW>::v>;
-    constexpr int NB = NarrowBytes<D, TX, TY, 4, (int)sizeof(E), SCHED>::v;
+    using G = BlockGeom<D, TX, TY>;
+    constexpr int NB = SCHED == 2 ? BlockSteps<D, TX, TY, NT, G::RWL, G::RH>::BYTES
+                                  : NarrowBytes<D, TX, TY, 4, (int)sizeof(E), SCHED>::v;
     __shared__ __attribute__((aligned(16))) uint8_t lds_raw[NB > W::BYTES ? NB : W::BYTES];
     __shared__ int s_bad;
     if (threadIdx.x == 0) s_bad = 0;
@@ -855,7 +1118,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(
     const int b = lb - d.block_start;
     const BlockPos bp = block_pos<TX, TY>(b % d.nbx, b / d.nbx, d.T);
     long long ca = 0, cs2 = 0;
-    __syncthreads();  // s_bad cleared
+    if constexpr (SCHED == 2) BlockSteps<D, TX, TY, NT, G::RWL, G::RH>::clear((int16_t *)lds_raw, d.N);
+    __syncthreads();  // s_bad (and the counts of steps) cleared
     if (__builtin_expect(!region_sweep<D, TX, TY, NT, E, SCHED>((E *)lds_raw, d, bp, t, ox, oy, &s_bad, ca, cs2,
                                                                  true, b), 0)) {
         if constexpr (!std::is_void<EW>::value)
@@ -1033,7 +1297,8 @@ __device__ __forceinline__ bool region_sweep16(E *lds, SurfDev &d, BlockPos bp, 
         ca += acc;
         cs2 += 2ll * (long long)q + (long long)acc + 2ll * base * acc;
     }
-    if (commit_here) commit_sweep<NT>(d, b, ca, cs2, t);
+    unsigned long long before = 0;
+    const bool last = commit_here && is_last(d, before = commit_sweep<NT>(d, b, ca, cs2));
 
     // ---- store: 16-byte chunks of 8 residues; 16-bit stores in the partial
     // chunks at both ends of each row
@@ -1092,6 +1357,7 @@ __device__ __forceinline__ bool region_sweep16(E *lds, SurfDev &d, BlockPos bp, 
             }
         }
     }
+    if (last) finish_sweep<true>(d, t);
     return true;
 }
 
@@ -1151,7 +1417,7 @@ __global__ void gather_records(const SurfDev *__restrict__ descs, int n, long lo
     const int k = (int)(blockIdx.x * blockDim.x + threadIdx.x);
     if (k >= n) return;
     const SurfDev &d = descs[k];
-    const long long *r = d.log + 3 * (d.t % d.log_cap);
+    const long long *r = d.log + 3 * d.slot;
     for (int i = 0; i < 3; ++i) out[3 * k + i] = r[i];
 }
 
@@ -1177,16 +1443,10 @@ __global__ void unpack16(const uint16_t *__restrict__ src, int32_t *__restrict__
 //
 // A small surface is bound by the chain of dependent attempts of a tile:
 // with one lane per tile L = 64 keeps 32 lanes of a CU busy, 64 attempts
-// after each other.  But attempts commute unless their sites are the same or
-// neighbours.  lds_run therefore first lays out each tile's attempts in
-// steps of up to four that are pairwise independent and keep their order
-// across steps (the site sequence does not depend on the heights, so this is
-// done by one lane per tile and Philox call, for L <= 64 by the waves that
-// would idle and one sweep ahead), then four lanes per tile make the attempts
-// of a step together.  D = 8: about 27 steps instead of 64, each one LDS
-// round trip and some 17 instructions of a wave that has its SIMD nearly to
-// itself.  Steps of eight would be about 20 at twice the lanes, which L = 128
-// does not have idle.
+// after each other.  So the attempts are made in steps (four lanes per tile);
+// for L <= 64 the waves that would idle lay the steps out, one sweep ahead.
+// Steps of eight would be about 20 at twice the lanes, which L = 128 does not
+// have idle.
 //
 // Heights are staged as 16-bit offsets from a base that follows the surface
 // (the restriction keeps the spread below N L, the mean rises by at most one
@@ -1201,7 +1461,6 @@ __global__ void unpack16(const uint16_t *__restrict__ src, int32_t *__restrict__
 // ---------------------------------------------------------------------------
 constexpr int kLdsRunMaxNL = 8192;
 constexpr int kLdsRebase = 4096;  // sweeps between moves of the base: 2 N L + kLdsRebase < 2^15
-constexpr int kLdsWin = 4;        // attempts per step
 constexpr int kLdsMaxL = 128;
 constexpr int kLdsThreads = 512;  // four lanes for each of the 128 tiles of a phase at L = 128, D = 8
 
@@ -1212,15 +1471,8 @@ struct LdsRun {
     // offsets; an odd number of words spreads the rows over the banks
     static constexpr int P = kLdsMaxL + 2 * D + 2;
     static_assert((P / 2) % 2 == 1, "odd words per row");
-    // Attempts of one Philox call, and of the last one of a tile.  Every
-    // lane of a tile has its own list of that many entries per call (a call
-    // may need a step for each of its attempts).
-    static constexpr int NPER = TB::PER < D * D ? TB::PER : D * D;
-    static constexpr int NLAST = D * D - (TB::NCALL - 1) * NPER;
-    static_assert(NPER % 2 == 0 && NLAST % 2 == 0, "entries are read in pairs");
-    // An entry is the LDS address of the site above the attempt's, in units
-    // of 2^SHIFT bytes, in 16 bits.
-    static constexpr int SHIFT = D == 32 ? 1 : 0;
+    static constexpr int SHIFT = D == 32 ? 1 : 0;  // of the lists' entries
+    static constexpr int NPER = StepList<D>::NPER, NLAST = StepList<D>::NLAST;
 
     __host__ __device__ static int lattice_rows(int L) { return L + 2 * D + 2 + 3; }  // and 3 of the idle lanes' site
     __host__ __device__ static int lattice_bytes(int L) { return (lattice_rows(L) * P * 2 + 15) & ~15; }
@@ -1240,66 +1492,6 @@ struct LdsRun {
         return lattice_bytes(L) + list_bytes(L, phases) * (ahead(L, phases) ? 2 : 1);
     }
 };
-
-typedef __attribute__((address_space(3))) int16_t l16;
-__device__ __forceinline__ uint32_t lds_address(const int16_t *p) { return (uint32_t)(uintptr_t)(const l16 *)p; }
-
-// a / d for 0 <= a < 2^20 with r = 1.0f / d: (a + 1/2) / d is at least
-// 1 / (2 d) from every integer, far more than the float error.
-__device__ __forceinline__ int div_by(int a, float r) { return (int)(((float)a + 0.5f) * r); }
-
-// Sum over the wavefront, in lane 63 (six dependent adds; an LDS atomic from
-// every lane took 9000 cycles per sweep).
-__device__ __forceinline__ int wave_sum63(int v)
-{
-    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, true);   // row_shr:1
-    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, true);   // row_shr:2
-    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, true);   // row_shr:4
-    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, true);   // row_shr:8
-    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, true);   // row_bcast:15
-    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, true);   // row_bcast:31
-    return v;
-}
-
-// Lays out the attempts of Philox call j of one tile in steps: the k-th step
-// takes entry k of the lists of the tile's kLdsWin lanes (`stride` entries
-// apart); the entries that are not used stay on the idle site.  `above` is
-// the site above the tile's corner.  Returns the number of steps.
-template <int D>
-__device__ __forceinline__ int lay_out_steps(uint16_t *list, int stride, const int16_t *above, int j, uint32_t tile_id,
-                                             uint32_t s, uint32_t p, uint32_t k0, uint32_t k1)
-{
-    using R = LdsRun<D>;
-    using TB = TileBits<D>;
-    const u32x4 r = philox4x32_10((uint32_t)j, tile_id, s, p, k0, k1);
-    const int n = j == TB::NCALL - 1 ? R::NLAST : R::NPER;
-    const uint32_t a0 = lds_address(above) >> R::SHIFT;
-    constexpr uint32_t FAR = 0x8080u;            // further than one bond from every site
-    uint32_t w1 = FAR, w2 = FAR, w3 = FAR;       // the step's sites so far, x + 256 y
-    int at = 0;                                  // entry of the next site
-    int used = 0, steps = 0;                     // sites of the current step, steps before it
-    static_assert(kLdsWin == 4, "three earlier sites are compared");
-#pragma unroll
-    for (int k = 0; k < R::NPER; ++k) {
-        if (k < n) {
-            const uint32_t f = (r.v[k / TB::F] >> ((k % TB::F) * TB::B)) & (uint32_t)(D * D - 1);
-            const uint32_t x = f & (uint32_t)(D - 1), y = f >> TB::LOG2D;
-            const uint32_t xy = x | (y << 8);
-            const uint32_t near = min(min(__builtin_amdgcn_sad_u8(xy, w1, 0), __builtin_amdgcn_sad_u8(xy, w2, 0)),
-                                      __builtin_amdgcn_sad_u8(xy, w3, 0));
-            const bool next = near <= 1u || used == kLdsWin;
-            w3 = next ? FAR : w2;
-            w2 = next ? FAR : w1;
-            w1 = xy;
-            steps += next;
-            at = next ? steps : at;
-            used = next ? 1 : used + 1;
-            list[at] = (uint16_t)(a0 + (__umul24(y, (uint32_t)R::P) + x) * 2 / (1 << R::SHIFT));
-            at += stride;
-        }
-    }
-    return steps + 1;
-}
 
 template <int D, int NT, int SCHED = 0>
 __global__ __launch_bounds__(NT) void lds_run(SurfDev *__restrict__ descs, const int *__restrict__ which)
@@ -1349,7 +1541,6 @@ __global__ __launch_bounds__(NT) void lds_run(SurfDev *__restrict__ descs, const
             const int y = i / L, x = i - y * L;
             h[(y < oy ? y + L : y) * P + (x < ox ? x + L : x)] = (int16_t)(src[i] - base);
         }
-        for (int i = tid; i < set / 2 * (ahead ? 2 : 1); i += NT) ((uint32_t *)lists)[i] = idle2;
         for (int i = tid; i < 2 * TB::NCALL * GROUPS; i += NT) (&s_steps[0][0][0])[i] = 0;
         if (tid < 4) s_sum[tid >> 1][tid & 1] = 0;
         if (tid == 0) {
@@ -1358,7 +1549,7 @@ __global__ __launch_bounds__(NT) void lds_run(SurfDev *__restrict__ descs, const
         }
     }
     // thread 0 keeps the sums
-    long long S1 = 0, S2 = 0, slot = t % d.log_cap;
+    long long S1 = 0, S2 = 0, slot = d.slot;
     if (tid == 0) {
         const long long *rec = d.log + 3 * slot;
         S1 = rec[0];
@@ -1395,8 +1586,8 @@ __global__ __launch_bounds__(NT) void lds_run(SurfDev *__restrict__ descs, const
             int tx, ty;
             tile_of(k, p + g, tx, ty);
             const int stride = j == TB::NCALL - 1 ? R::NLAST : R::NPER;
-            const int n = lay_out_steps<D>(lists + half * set + j * R::NPER * all * kLdsWin + i2 * kLdsWin * stride,
-                                           stride, h + (y + ty * D - 1) * P + x + tx * D, j, (uint32_t)(ty * T + tx), s,
+            const int n = lay_out_steps<D, P, R::SHIFT>(lists + half * set + j * R::NPER * all * kLdsWin + i2 * kLdsWin * stride,
+                                           stride, h + (y + ty * D - 1) * P + x + tx * D, idle2, j, (uint32_t)(ty * T + tx), s,
                                            (uint32_t)(SCHED == 0 ? p + g : 4 + p + g), k0, k1);
             atomicMax(&s_steps[half][j][g * ngroups + (k >> 4)], n);
         }
@@ -1426,29 +1617,9 @@ __global__ __launch_bounds__(NT) void lds_run(SurfDev *__restrict__ descs, const
                 for (int j = 0; j < TB::NCALL; ++j) {
                     const int n = __builtin_amdgcn_readfirstlane(nsteps[j * GROUPS]);
                     const int stride = j == TB::NCALL - 1 ? R::NLAST : R::NPER;
-                    uint32_t *e = (uint32_t *)(e0 + j * R::NPER * all * kLdsWin +
+                    const uint32_t *e = (const uint32_t *)(e0 + j * R::NPER * all * kLdsWin +
                                                ((g * ntiles + k) * kLdsWin + (tid & (kLdsWin - 1))) * stride);
-                    uint32_t two = *e;
-                    auto attempt1 = [&](uint32_t a) {
-                        // the site above, then the site and its neighbours at constant offsets
-                        l16 *c = (l16 *)(uintptr_t)(a << R::SHIFT);
-                        const int u = c[0], l = c[P - 1], v = c[P], r = c[P + 1], w = c[2 * P];
-                        const int n1 = min(v + 1, min(min(l, r), min(u, w)) + N);
-                        c[P] = (int16_t)n1;
-                        const int ok = n1 - v;
-                        acc += ok;
-                        q += __mul24(v, ok);
-                        // the next step's reads stay behind these writes
-                        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                    };
-#pragma unroll 1
-                    for (int step = 0; step < n; step += 2) {
-                        const uint32_t cur = two;
-                        two = e[1];  // (one pair beyond the last step's is read, and not used)
-                        *e++ = idle2;
-                        attempt1(cur & 0xFFFFu);
-                        attempt1(cur >> 16);
-                    }
+                    make_steps<P, R::SHIFT>(e, n, N, acc, q);
                     nsteps[j * GROUPS] = 0;
                 }
             }
@@ -1513,7 +1684,10 @@ __global__ __launch_bounds__(NT) void lds_run(SurfDev *__restrict__ descs, const
             dst[i] = base + h[(y < oy ? y + L : y) * P + (x < ox ? x + L : x)];
         }
     }
-    if (tid == 0) d.t = t_end;
+    if (tid == 0) {
+        d.t = t_end;
+        d.slot = slot;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1617,7 +1791,10 @@ __global__ __launch_bounds__(NT) void lds_run32(SurfDev *__restrict__ descs, con
         int32_t *dst = d.buf[t_end & 1];
         for (int i = threadIdx.x; i < n; i += NT) dst[i] = lat[i];
     }
-    if (threadIdx.x == 0) d.t = t_end;
+    if (threadIdx.x == 0) {
+        d.t = t_end;
+        d.slot = t_end % d.log_cap;
+    }
 }
 
 }  // namespace rsosk
