@@ -742,9 +742,9 @@ struct SurfaceGroup {
         const SurfDev &s = host[i];
         const long long n = (long long)s.L * s.L;
         // at most 2^16 sites per thread: grid >= n / 2^24
-        const int grid = (int)std::min<long long>(kPsGrid, std::max<long long>(1, n / (256 * 64)));
+        const int grid = (int)std::min<long long>(kPsGrid, std::max<long long>(1, n / (256 * 32)));
         rsos_status st;
-        if (!d_ps && (st = dev_alloc((void **)&d_ps, sizeof(long long) * (8 * (size_t)kPsGrid + 8))) != RSOS_OK)
+        if (!d_ps && (st = dev_alloc((void **)&d_ps, sizeof(long long) * (8 * (size_t)kPsGrid + 9))) != RSOS_OK)
             return st;
         const long long *rec = s.log + 3 * (s.t % s.log_cap);
         if (packed)
@@ -754,17 +754,16 @@ struct SurfaceGroup {
             hipLaunchKernelGGL(rsosk::power_sums_partial<int32_t>, dim3(grid), dim3(256), 0, stream,
                                (const int32_t *)s.buf[s.t & 1], n, rec, d_ps);
         HIP_TRY(hipGetLastError());
-        hipLaunchKernelGGL(rsosk::power_sums_final, dim3(1), dim3(256), 0, stream, d_ps, grid,
-                           d_ps + 8 * (size_t)kPsGrid);
+        long long *total = d_ps + 8 * (size_t)kPsGrid;  // 4 int128, then S1
+        hipLaunchKernelGGL(rsosk::power_sums_final, dim3(1), dim3(256), 0, stream, d_ps, grid, rec, total);
         HIP_TRY(hipGetLastError());
-        rsos_width_t w;
-        if ((st = read_log(i, s.t, 1, &w)) != RSOS_OK) return st;  // synchronises
-        unsigned long long r[8];
-        HIP_TRY(hipMemcpy(r, d_ps + 8 * (size_t)kPsGrid, sizeof r, hipMemcpyDeviceToHost));
+        if ((st = staging.copy_from(total, sizeof(long long) * 9, stream)) != RSOS_OK) return st;
+        unsigned long long r[9];
+        memcpy(r, staging.host, sizeof r);
         __int128 c[4];
         for (int k = 0; k < 4; ++k) c[k] = (__int128)(((unsigned __int128)r[2 * k + 1] << 64) | r[2 * k]);
         out->t = s.t;
-        out->ref = w.s1 / n;
+        out->ref = (long long)r[8] / n;
         out->c1 = (int64_t)c[0];
         out->c2 = (int64_t)c[1];
         out->c3[0] = r[4];

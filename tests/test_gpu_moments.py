@@ -107,3 +107,27 @@ def test_full_size_moments(rsos, oracle):
     p = rsos.Surface(L, N=N, seed=seed, D=D, packed=True)
     p.sweep(cfg.sweeps)
     assert p.moments() == g
+
+
+@pytest.mark.parametrize("shift", [0, 1])
+@pytest.mark.parametrize("L,N,amp", [(256, 1, 1), (384, 4, 4), (1024, 30, 30)])
+def test_packed_readout_alignment(rsos, L, N, amp, shift):
+    """16-bit storage: heights go in and come out through int32 buffers that
+    are 16-byte aligned or not, with spreads that leave a byte."""
+    import ctypes
+
+    import torch
+    from paper_1605_02620_amd import _lib
+    if N * 8 > 96:
+        N = 12
+    h0 = workloads.rough(L, N, seed=L, base=70000)
+    print(f"[moments] readout L={L} N={N} shift={shift}", flush=True)
+    s = rsos.Surface(L, N=N, seed=5, D=8, h0=h0, packed=True)
+    out = torch.zeros(L * L + 4, dtype=torch.int32, device="cuda")
+    _lib.check(_lib.lib().rsos_heights(s._h, ctypes.c_void_p(out.data_ptr() + 4 * shift), 1))
+    assert np.array_equal(out[shift:shift + L * L].cpu().numpy(), h0)
+    assert int(out[:shift].abs().sum()) == 0 and int(out[shift + L * L:].abs().sum()) == 0
+    m = s.moments()
+    d = h0.astype(np.int64) - int(h0.astype(np.int64).sum()) // (L * L)
+    assert [m["c1"], m["c2"], m["c3"], m["c4"]] == [int((d ** k).sum()) for k in (1, 2, 3, 4)]
+    s.close()
