@@ -166,7 +166,6 @@ __device__ __forceinline__ void attempt(E *lds, int base, uint32_t f, int N, int
 {
     constexpr int LOG2D = TileBits<D>::LOG2D;
     const int idx = base + (int)(f >> LOG2D) * P + (int)(f & (D - 1));
-    int c, m;
     if constexpr (std::is_same<E, uint8_t>::value) {
         // unsigned byte staging (LDS-bound): the left neighbour, the site and
         // the right neighbour from one read of the two aligned words around
@@ -181,41 +180,43 @@ __device__ __forceinline__ void attempt(E *lds, int base, uint32_t f, int N, int
         uint32_t lr;
         asm("v_min_u16_sdwa %0, %1, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_0 src1_sel:BYTE_2"
             : "=v"(lr) : "v"(t3));
-        c = (int)((t3 >> 8) & 0xFFu);
-        m = (int)min(min(lr, (uint32_t)lds[i1 + 1 - P]), (uint32_t)lds[i1 + 1 + P]);
-        // all ones if accepted, else zero
-        const int nok = (c - m - N) >> 31;
-        // c & nok and c - nok with c taken as byte 1 of t3 by the
-        // instructions themselves
-        int qc, cn;
+        const int d1 = (int)lds[i1 + 1 - P], d2 = (int)lds[i1 + 1 + P];
+        // the new height is min(c + 1, m + N), m the least neighbour: accepted
+        // iff c + 1 <= m + N, and c <= m + N always
+        int n1;
+        asm("v_add_u32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_1"
+            : "=v"(n1) : "v"(1 - N), "v"(t3));
+        n1 = min(min(min(n1, (int)lr), d1), d2) + N;
+        lds[i1 + 1] = (E)n1;
+        // all ones if accepted, else zero; then c where accepted
+        int nok, qc;
+        asm("v_sub_u32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_1 src1_sel:DWORD"
+            : "=v"(nok) : "v"(t3), "v"(n1));
         asm("v_and_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_1"
             : "=v"(qc) : "v"(nok), "v"(t3));
-        asm("v_sub_u32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_1 src1_sel:DWORD"
-            : "=v"(cn) : "v"(t3), "v"(nok));
         q += qc;
-        lds[i1 + 1] = (E)cn;
         // this staging counts acceptances negatively (one instruction less
         // per attempt); region_sweep16 negates the block's count
         acc += nok;
         return;
     } else {
-        c = lds[idx];
-        m = min(min((int)lds[idx - 1], (int)lds[idx + 1]), min((int)lds[idx - P], (int)lds[idx + P]));
+        const int c = lds[idx], l = lds[idx - 1], r = lds[idx + 1], u = lds[idx - P], w = lds[idx + P];
+        if constexpr (sizeof(E) <= 2) {
+            // narrow staging: N is far inside int range (see above)
+            const int n1 = min(min(min(min(c + 1 - N, l), r), u), w) + N;
+            lds[idx] = (E)n1;
+            const int ok = n1 - c;
+            q += __mul24(c, ok);
+            acc += ok;
+        } else {
+            // h_c + 1 - h_j <= N for every neighbour j; the lower side cannot
+            // fail because |h_c - h_j| <= N held before
+            const int ok = (c - min(min(l, r), min(u, w))) < N;
+            q += ok ? (Q)c : (Q)0;
+            lds[idx] = (E)(c + ok);
+            acc += ok;
+        }
     }
-    // h_c + 1 - h_j <= N for every neighbour j; the lower side cannot fail
-    // because |h_c - h_j| <= N held before.
-    int ok;
-    if constexpr (sizeof(E) <= 2) {
-        // narrow staging: c - m and N are far inside int range, so the sign
-        // of c - m - N decides
-        ok = (int)((uint32_t)(c - m - N) >> 31);
-        q += __mul24(c, ok);
-    } else {
-        ok = (c - m) < N;
-        q += ok ? (Q)c : (Q)0;
-    }
-    lds[idx] = (E)(c + ok);
-    acc += ok;
 }
 
 // D^2 sequential attempts of one tile: the Philox calls whose fields are
