@@ -223,6 +223,73 @@ const Variant *pick_variant(int D, const std::vector<std::pair<int, int>> &LN, b
     return least;
 }
 
+// Block shapes of the launches of two sweeps (int32 storage, tile
+// checkerboard, D = 8), each for up to per_cu blocks per CU, in order of the
+// time that a pair takes at that count.  Per sweep, two per launch against
+// one (us):
+//     32 x 8,  1 per CU   L = 1360: 16.7 / 18.8, L = 2048: 18.8 / 23.2, 64 surfaces of 256: 18.9 / 20.7
+//     32 x 16, 1 per CU   L = 2560: 22.8 / 27.4, 8 surfaces of 1024: 23.3 / 28.7
+//     32 x 8,  3 per CU   L = 3072: 32.7 / 34.6
+//     32 x 16, 2 per CU   L = 4096: 36.4 / 42.4, 64 surfaces of 512: 35.6 / 43.1
+// With more blocks the attempts themselves are the bound, of which a pair
+// makes more: L = 5120 60.9 / 59.3, L = 8192 118.4 / 116.5, L = 16384
+// 431 / 406.
+struct Pair {
+    int D, TX, TY, NT, per_cu;
+    void (*launch)(dim3, hipStream_t, SurfDev *, int, const int *, int, int);
+};
+
+template <int D, int TX, int TY, int NT>
+void launch_pair(dim3 grid, hipStream_t st, SurfDev *d, int n, const int *owner, int xmode, int xnbx)
+{
+    hipLaunchKernelGGL((rsosk::block_sweep2<D, TX, TY, NT>), grid, dim3(NT), 0, st, d, n, owner, xmode, xnbx);
+}
+
+#define PAIR(D, TX, TY, NT, PER) {D, TX, TY, NT, PER, launch_pair<D, TX, TY, NT>}
+const Pair kPairs[] = {PAIR(8, 32, 8, 256, 1), PAIR(8, 32, 16, 512, 1), PAIR(8, 32, 8, 256, 3), PAIR(8, 32, 16, 512, 2)};
+#undef PAIR
+
+bool pair_fits(const Pair &q, int L, int N)
+{
+    const int ring = 2 * (q.D + 1), rw = (q.TX + rsosk::kTwoMargin) * q.D + ring, rh = (q.TY + rsosk::kTwoMargin) * q.D + ring;
+    const int rwl = (rw + 6) & ~3;
+    // (as in variant_fits)
+    if (L < q.TX * q.D || rh > L || (rwl > L && !(q.TX * q.D == L && rwl <= 2 * L))) return false;
+    return 2ll * N * q.D <= 96 && (long long)N * (rw + rh + 4) + 2 * q.D * q.D <= 32767;
+}
+
+// The shape for two sweeps per launch of surfaces (L, N), or nullptr (also
+// where RSOS_VARIANT names the kernel to run).
+const Pair *pick_pair(int D, const std::vector<std::pair<int, int>> &LN)
+{
+    if (getenv("RSOS_VARIANT")) return nullptr;
+    // Up to one block of 8 x 8 tiles per CU, single sweeps in steps are as
+    // fast or faster (L = 512: 14.3 / 16.5 us, L = 1024: 17.0 / 17.0).
+    long long small = 0;
+    for (auto &ln : LN) small += (long long)blocks_along(ln.first / D, 8) * blocks_along(ln.first / D, 8);
+    if (small <= kCUs) return nullptr;
+    for (const Pair &q : kPairs) {
+        if (q.D != D) continue;
+        bool ok = true;
+        long long blocks = 0;
+        for (auto &ln : LN) {
+            ok = ok && pair_fits(q, ln.first, ln.second);
+            blocks += (long long)blocks_along(ln.first / D, q.TX) * blocks_along(ln.first / D, q.TY);
+        }
+        if (ok && blocks <= q.per_cu * kCUs) return &q;
+    }
+    return nullptr;
+}
+
+// A surface's blocks of shape q, the first of them number start.
+int place_pair(SurfDev &d, const Pair &q, long long start)
+{
+    d.nbx2 = blocks_along(d.T, q.TX);
+    d.nblocks2 = d.nbx2 * blocks_along(d.T, q.TY);
+    d.block_start2 = (int)start;
+    return d.nblocks2;
+}
+
 bool uses_lds(int L);
 
 // 16-bit storage is exact while every height of a sweep stays within 2^15
@@ -378,6 +445,9 @@ struct Shape {
     int first = 0, count = 0;
     int total_blocks = 0;
     int *d_owner = nullptr;  // block -> row within the shape (count > 1)
+    const Pair *pair = nullptr;  // blocks of its launches of two sweeps (nullptr: none)
+    int pair_blocks = 0, pair_xmode = 1;
+    int *d_owner2 = nullptr; // as d_owner
 };
 
 // A launch choice for one surface: kernel variant, block order and sweeps
@@ -416,8 +486,10 @@ struct SurfaceGroup {
     size_t lds_bytes = 0;
     bool lds_is_wide = false;
     Staging staging;
-    hipGraphExec_t graph = nullptr;
-    int graph_sweeps = 0;
+    bool pairs = true;                 // two sweeps may share a launch
+    bool any_pair = false;             // and do, in some shape
+    hipGraphExec_t graph = nullptr;    // graph_k sweeps that every block-path surface makes
+    hipGraphExec_t graph1 = nullptr;   // as many, one per launch, each bounded by t_end (where it differs)
     bool timing = false;                             // bracket block launches with events
     std::vector<std::pair<hipEvent_t, hipEvent_t>> timed;
     std::vector<void *> owned;         // library-owned device allocations
@@ -481,6 +553,13 @@ struct SurfaceGroup {
             sh.first = (int)rows.size();
             sh.count = (int)members[g].size();
             long long blocks = 0;
+            long long blocks2 = 0;
+            if (pairs && !packed && sched == 0) {
+                std::vector<std::pair<int, int>> ln;
+                for (int i : members[g]) ln.push_back({host[i].L, host[i].N});
+                sh.pair = pick_pair(D, ln);
+                any_pair = any_pair || sh.pair;
+            }
             for (int i : members[g]) {
                 SurfDev &sd = host[i];
                 const int T = sd.L / D;
@@ -488,10 +567,13 @@ struct SurfaceGroup {
                 sd.nblocks = sd.nbx * blocks_along(T, sh.variant->TY);
                 sd.block_start = (int)blocks;
                 blocks += sd.nblocks;
+                if (sh.pair) blocks2 += place_pair(sd, *sh.pair, blocks2);
                 if (blocks > (1ll << 30)) return fail(RSOS_E_INVAL, "too many tile blocks");
                 rows.push_back(i);
             }
             sh.total_blocks = (int)blocks;
+            sh.pair_blocks = (int)blocks2;
+            sh.pair_xmode = sh.xmode == 2 && sh.pair && !(sh.count == 1 && host[members[g][0]].nbx2 % 8 == 0) ? 1 : sh.xmode;
             if (sh.xmode == 2 && !(sh.count == 1 && host[members[g][0]].nbx % 8 == 0)) sh.xmode = 1;
         }
         const int nblk_rows = (int)rows.size();
@@ -512,13 +594,16 @@ struct SurfaceGroup {
         for (Shape &sh : shapes) {
             if (sh.count < 2) continue;
             // owner of every block of the shape: its row within the shape
-            std::vector<int> own((size_t)sh.total_blocks);
+            // (and of every block of two sweeps)
+            std::vector<int> own((size_t)sh.total_blocks + sh.pair_blocks);
             for (int k = 0; k < sh.count; ++k) {
                 const SurfDev &sd = host[rows[sh.first + k]];
                 for (int b = 0; b < sd.nblocks; ++b) own[(size_t)sd.block_start + b] = k;
+                for (int b = 0; b < sd.nblocks2; ++b) own[(size_t)sh.total_blocks + sd.block_start2 + b] = k;
             }
             if ((st = dev_alloc((void **)&sh.d_owner, sizeof(int) * own.size())) != RSOS_OK) return st;
             HIP_TRY(hipMemcpy(sh.d_owner, own.data(), sizeof(int) * own.size(), hipMemcpyHostToDevice));
+            sh.d_owner2 = sh.d_owner + sh.total_blocks;
         }
         if (!lds_idx.empty()) {
             if ((st = dev_alloc((void **)&d_lds_idx, sizeof(int) * lds_idx.size())) != RSOS_OK) return st;
@@ -574,17 +659,30 @@ struct SurfaceGroup {
             HIP_TRY(hipGetLastError());
         }
         if (blk_idx.empty()) return RSOS_OK;
+        // sweeps that every block-path surface makes: only these may be
+        // launched two at a time
+        long long every = n;
+        for (int i : blk_idx) every = std::min(every, host[i].t_end - host[i].t);
+        if (!any_pair) every = n;
+        rsos_status st = run_block(every, &graph, any_pair);
+        if (st == RSOS_OK) st = run_block(n - every, &graph1, false);
+        return st;
+    }
+
+    // n sweeps of the tile blocks, as replays of a graph of graph_k sweeps
+    // where there are enough of them, four: in pairs per launch.
+    rsos_status run_block(long long n, hipGraphExec_t *gr, bool four)
+    {
         long long left = n;
         if (stream != nullptr && n >= 2 * graph_k && !timing) {
-            if (!graph) {
-                rsos_status st = capture_graph(graph_k);
+            if (!*gr) {
+                rsos_status st = capture_graph(graph_k, gr, four);
                 if (st != RSOS_OK) return st;
             }
-            while (left >= graph_sweeps) {
-                HIP_TRY(hipGraphLaunch(graph, stream));
-                left -= graph_sweeps;
-            }
+            for (; left >= graph_k; left -= graph_k) HIP_TRY(hipGraphLaunch(*gr, stream));
         }
+        for (; four && !timing && left >= 4; left -= 4) launch_four();
+        HIP_TRY(hipGetLastError());
         for (; left > 0; --left) {
             rsos_status st = enqueue_one();
             if (st != RSOS_OK) return st;
@@ -592,18 +690,32 @@ struct SurfaceGroup {
         return RSOS_OK;
     }
 
+    // four sweeps of every surface, two per launch where the shape takes them
+    void launch_four()
+    {
+        for (const Shape &sh : shapes) {
+            const int nbx2 = sh.count == 1 ? host[rows[sh.first]].nbx2 : 0;
+            for (int i = 0; i < 4; ++i)
+                if (!sh.pair) launch_shape(sh);
+                else if (i % 2 == 0)
+                    sh.pair->launch(dim3(sh.pair_blocks), stream, d_desc + sh.first, sh.count, sh.d_owner2, sh.pair_xmode, nbx2);
+        }
+    }
+
+    void launch_shape(const Shape &sh, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr)
+    {
+        const Variant *v = sh.variant;
+        BlockLaunch k = packed ? v->launch16 : sched == 1 ? v->launch_dt : v->launch;
+        const int nbx = sh.count == 1 ? host[rows[sh.first]].nbx : 0;
+        k(dim3(sh.total_blocks), stream, d_desc + sh.first, sh.count, sh.d_owner, sh.xmode, nbx, e0, e1);
+    }
+
     // the tile-block sweep proper: one workgroup per block, the whole sweep
     // in one launch per kernel instance
     void launch_block_sweep(hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr)
     {
-        for (size_t i = 0; i < shapes.size(); ++i) {
-            const Shape &sh = shapes[i];
-            const Variant *v = sh.variant;
-            BlockLaunch k = packed ? v->launch16 : sched == 1 ? v->launch_dt : v->launch;
-            const int nbx = sh.count == 1 ? host[rows[sh.first]].nbx : 0;
-            k(dim3(sh.total_blocks), stream, d_desc + sh.first, sh.count, sh.d_owner, sh.xmode, nbx,
-              i == 0 ? e0 : nullptr, i + 1 == shapes.size() ? e1 : nullptr);
-        }
+        for (size_t i = 0; i < shapes.size(); ++i)
+            launch_shape(shapes[i], i == 0 ? e0 : nullptr, i + 1 == shapes.size() ? e1 : nullptr);
     }
 
     rsos_status enqueue_one()
@@ -626,18 +738,18 @@ struct SurfaceGroup {
     rsos_status prepare_graph()
     {
         if (stream == nullptr || blk_idx.empty() || graph) return RSOS_OK;
-        return capture_graph(graph_k);
+        return capture_graph(graph_k, &graph, any_pair);
     }
 
-    rsos_status capture_graph(int k)
+    rsos_status capture_graph(int k, hipGraphExec_t *gr, bool four)
     {
         hipGraph_t g = nullptr;
         HIP_TRY(hipStreamBeginCapture(stream, hipStreamCaptureModeThreadLocal));
-        for (int i = 0; i < k; ++i) launch_block_sweep();
+        for (; four && k >= 4; k -= 4) launch_four();
+        for (; k > 0; --k) launch_block_sweep();
         HIP_TRY(hipStreamEndCapture(stream, &g));
-        HIP_TRY(hipGraphInstantiate(&graph, g, nullptr, nullptr, 0));
+        HIP_TRY(hipGraphInstantiate(gr, g, nullptr, nullptr, 0));
         HIP_TRY(hipGraphDestroy(g));
-        graph_sweeps = k;
         return RSOS_OK;
     }
 
@@ -819,6 +931,7 @@ struct SurfaceGroup {
         else (void)hipDeviceSynchronize();
         clear_timing();
         if (graph) (void)hipGraphExecDestroy(graph);
+        if (graph1) (void)hipGraphExecDestroy(graph1);
         staging.release();
         for (void *p : owned) (void)hipFree(p);
         owned.clear();
@@ -1219,7 +1332,7 @@ constexpr size_t kScratchBytes = 128 * 1024;
 constexpr size_t kScratchDesc = 0;      // SurfDev
 constexpr size_t kScratchIdx = 128;     // int 0: the LDS-path kernel's descriptor index
 constexpr size_t kScratchAcc = 256;     // kAccWords int64
-constexpr size_t kScratchLog = 2048;    // log ring of kStaticLogCap records of 3 int64
+constexpr size_t kScratchLog = 4096;    // log ring of kStaticLogCap records of 3 int64
 constexpr long long kStaticLogCap = RSOS_STATIC_MAX_SWEEPS + 1;
 static_assert(sizeof(SurfDev) <= kScratchIdx, "descriptor slot");
 static_assert(kScratchAcc + 8 * rsosk::kAccWords <= kScratchLog, "accumulator slot");
@@ -1315,12 +1428,15 @@ extern "C" rsos_status rsos_sweep_static(const rsos_params *p, int32_t *d_h, int
     d.N = p->N;
     d.T = p->L / D;
     const Variant *v = nullptr;
+    const Pair *pair = nullptr;
     if (!uses_lds(p->L)) {
         v = pick_variant(D, {{p->L, p->N}}, false, sched == 1);
         if (!v) return fail(RSOS_E_INVAL, "no tile-block shape fits L=%d, N=%d, D=%d", p->L, p->N, D);
         d.nbx = blocks_along(d.T, v->TX);
         d.nblocks = d.nbx * blocks_along(d.T, v->TY);
         d.block_start = 0;
+        if (sched == 0) pair = pick_pair(D, {{p->L, p->N}});
+        if (pair) place_pair(d, *pair, 0);
     }
     hipStream_t s = (hipStream_t)stream;
     SurfDev *dd = (SurfDev *)(base + kScratchDesc);
@@ -1335,7 +1451,10 @@ extern "C" rsos_status rsos_sweep_static(const rsos_params *p, int32_t *d_h, int
         HIP_TRY(hipGetLastError());
     } else {
         BlockLaunch k = sched == 1 ? v->launch_dt : v->launch;
-        for (long long i = 0; i < n_mcs; ++i) k(dim3(d.nblocks), s, dd, 1, nullptr, 1, d.nbx, nullptr, nullptr);
+        long long left = n_mcs;
+        for (; pair && left >= 4; left -= 4)
+            for (int i = 0; i < 2; ++i) pair->launch(dim3(d.nblocks2), s, dd, 1, nullptr, 1, d.nbx2);
+        for (; left > 0; --left) k(dim3(d.nblocks), s, dd, 1, nullptr, 1, d.nbx, nullptr, nullptr);
         HIP_TRY(hipGetLastError());
     }
     const unsigned grid = (unsigned)std::min<long long>((3 * n_mcs + 255) / 256, 64);

@@ -77,14 +77,15 @@ __host__ __device__ __forceinline__ u32x4 philox4x32_10(uint32_t c0, uint32_t c1
 // block (or lds_run) advances t.
 // ---------------------------------------------------------------------------
 constexpr int kAccSlots = 64;  // per-surface spread of the (S1, S2) atomics
-// Per-surface accumulator area: 2 * kAccSlots words of increments, then
+// Per-surface accumulator area: 4 * kAccSlots words of increments (two pairs
+// for a launch of two sweeps), then
 // word kMeanWord = floor(S1 / L^2) of the current time (16-bit storage only,
 // which recovers true heights from it: kept by the sweep's last block, read
 // by every block) and, in a 128-byte line of its own so that the blocks'
 // atomic additions to it do not stall those reads, word kDoneWord, the
 // blocks of the running sweep that have committed.  All words but
 // kMeanWord are zero between sweeps.  Areas are 128-byte aligned.
-constexpr int kMeanWord = 2 * kAccSlots;
+constexpr int kMeanWord = 4 * kAccSlots;
 constexpr int kDoneWord = kMeanWord + 16;
 constexpr int kAccWords = kDoneWord + 16;
 
@@ -115,18 +116,20 @@ __device__ __forceinline__ void store4(gint32 *p, const int4 v)
 }
 
 struct SurfDev {
-    int32_t *buf[2];      // state after t sweeps is in buf[t & 1]
+    int32_t *buf[2];      // state after t sweeps is in buf[t & 1] (see flip)
     long long *log;       // 3 * log_cap int64: (S1, S2, A) of time tau at slot tau % log_cap
     long long *acc;       // kAccWords int64: accumulators (zero between sweeps), mean floor
     long long log_cap;
     long long t;          // sweeps done
     long long slot;       // t % log_cap
     long long t_end;      // run while t < t_end
+    long long flip;       // the state of time t is in buf[(t + flip) & 1]; 0 but between two launches of two sweeps
     uint32_t key0, key1;  // Philox key = seed
     int L, N, T;          // T = L / D
     int nbx;              // blocks along x (block path)
     int nblocks;          // blocks of this surface (block path)
     int block_start;      // first global block index of this surface
+    int nbx2, nblocks2, block_start2;  // the same for the launches of two sweeps, whose blocks have a shape of their own
 };
 
 template <int D>
@@ -332,13 +335,14 @@ __device__ __forceinline__ void store4_stream(gint32 *dst, const int4 v)
 // Descriptor index of the surface that owns global block lb: from the
 // host-built table when there is one (one load), else by binary search over
 // the descriptors (sorted by block_start).
+template <bool TWO = false>
 __device__ __forceinline__ int find_surface(const SurfDev *descs, int nsurf, const int *owner, int lb)
 {
     if (owner) return owner[lb];
     int lo = 0, hi = nsurf - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
-        if (descs[mid].block_start <= lb) lo = mid; else hi = mid - 1;
+        if ((TWO ? descs[mid].block_start2 : descs[mid].block_start) <= lb) lo = mid; else hi = mid - 1;
     }
     return lo;
 }
@@ -718,59 +722,63 @@ __device__ __forceinline__ long long wave_sum63_64(long long v)
     return v;
 }
 
-// Wave 0 of the block that completed the count.
-template <bool MEAN>
+// Wave 0 of the block that completed the count of a launch of NS sweeps.
+template <bool MEAN, int NS = 1>
 __device__ __forceinline__ void finish_sweep(SurfDev &d, long long t)
 {
     const int lane = threadIdx.x;  // < 64
     const gi64 *prev = (const gi64 *)(d.log + 3 * d.slot);
-    const long long p1 = prev[0], p2 = prev[1];
-    gu64 *a = (gu64 *)(d.acc + 2 * lane);
-    long long x = (long long)__hip_atomic_load(a + 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    long long y = (long long)__hip_atomic_load(a + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(a + 0, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(a + 1, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    x = wave_sum63_64(x);
-    y = wave_sum63_64(y);
+    long long S1 = prev[0], S2 = prev[1];
+    gu64 *a = (gu64 *)(d.acc + 4 * lane);
+    long long x[2 * NS];
+#pragma unroll
+    for (int i = 0; i < 2 * NS; ++i) x[i] = (long long)__hip_atomic_load(a + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+    for (int i = 0; i < 2 * NS; ++i) __hip_atomic_store(a + i, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+    for (int i = 0; i < 2 * NS; ++i) x[i] = wave_sum63_64(x[i]);
     if (lane == 63) {
-        const long long slot = d.slot + 1 == d.log_cap ? 0 : d.slot + 1;
-        gi64 *e = (gi64 *)(d.log + 3 * slot);
-        e[0] = p1 + x;
-        e[1] = p2 + y;
-        e[2] = x;
-        if constexpr (MEAN) *(gi64 *)(d.acc + kMeanWord) = (p1 + x) / ((long long)d.L * d.L);
+        long long slot = d.slot;
+#pragma unroll
+        for (int k = 0; k < NS; ++k) {
+            slot = slot + 1 == d.log_cap ? 0 : slot + 1;
+            gi64 *e = (gi64 *)(d.log + 3 * slot);
+            e[0] = S1 += x[2 * k];
+            e[1] = S2 += x[2 * k + 1];
+            e[2] = x[2 * k];
+        }
+        if constexpr (MEAN) *(gi64 *)(d.acc + kMeanWord) = S1 / ((long long)d.L * d.L);
         __hip_atomic_store((gu64 *)(d.acc + kDoneWord), 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        *(gi64 *)&d.t = t + 1;
+        *(gi64 *)&d.t = t + NS;
         *(gi64 *)&d.slot = slot;
+        if (NS == 2) *(gi64 *)&d.flip = d.flip ^ 1;
     }
 }
 
-// a = this thread's accepted count, s2 = its share of the S2 increment.
-// Called by the whole workgroup once its sums are final.  Returns, in
-// thread 0, the number of the surface's blocks counted before this one.
-template <int NT>
-__device__ __forceinline__ unsigned long long commit_sweep(SurfDev &d, int b, long long a, long long s2)
+// inc: this thread's accepted count and its share of the S2 increment, for
+// each sweep of the launch.  Called by the whole workgroup once its sums are
+// final.  Returns, in thread 0, the number of the surface's blocks counted
+// before this one.
+template <int NT, int NS = 1>
+__device__ __forceinline__ unsigned long long commit_sweep(SurfDev &d, int b, long long (&inc)[2 * NS])
 {
-    __shared__ long long red[2][NT / 64];
-    a = wave_sum63_64(a);
-    s2 = wave_sum63_64(s2);
-    if ((threadIdx.x & 63) == 63) {
-        red[0][threadIdx.x >> 6] = a;
-        red[1][threadIdx.x >> 6] = s2;
+    __shared__ long long red[2 * NS][NT / 64];
+#pragma unroll
+    for (int i = 0; i < 2 * NS; ++i) {
+        inc[i] = wave_sum63_64(inc[i]);
+        if ((threadIdx.x & 63) == 63) red[i][threadIdx.x >> 6] = inc[i];
     }
     __syncthreads();
     unsigned long long before = 0;
     if (threadIdx.x == 0) {
-        a = red[0][0];
-        s2 = red[1][0];
-        for (int i = 1; i < NT / 64; ++i) {
-            a += red[0][i];
-            s2 += red[1][i];
+        gu64 *slot = (gu64 *)(d.acc + 4 * (b & (kAccSlots - 1)));
+#pragma unroll
+        for (int i = 0; i < 2 * NS; ++i) {
+            long long v = red[i][0];
+            for (int w = 1; w < NT / 64; ++w) v += red[i][w];
+            __hip_atomic_fetch_add(slot + i, (unsigned long long)v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
-        gu64 *slot = (gu64 *)(d.acc + 2 * (b & (kAccSlots - 1)));
-        __hip_atomic_fetch_add(slot + 0, (unsigned long long)a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_fetch_add(slot + 1, (unsigned long long)s2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        // the two additions are performed before the block is counted
+        // the additions are performed before the block is counted
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         before = __hip_atomic_fetch_add((gu64 *)(d.acc + kDoneWord), 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
@@ -779,9 +787,9 @@ __device__ __forceinline__ unsigned long long commit_sweep(SurfDev &d, int b, lo
 
 // Whether this block completed the count (wave 0; false in the others).
 // Waits for the count, and for every store that wave 0 has made before.
-__device__ __forceinline__ bool is_last(const SurfDev &d, unsigned long long before)
+__device__ __forceinline__ bool is_last(int nblocks, unsigned long long before)
 {
-    return threadIdx.x < 64 && __builtin_amdgcn_readfirstlane((int)(before + 1 == (unsigned long long)d.nblocks)) != 0;
+    return threadIdx.x < 64 && __builtin_amdgcn_readfirstlane((int)(before + 1 == (unsigned long long)nblocks)) != 0;
 }
 
 // Workgroup -> global block.  Mode 1: the dispatcher hands consecutive
@@ -890,6 +898,79 @@ struct WideOcc {
     static constexpr int v = (EWS == 0 || D != 8) ? 1 : (w < 1 ? 1 : w);
 };
 
+// Stores a staged block of TX x TY tiles: its first site is at LDS row row0
+// and column off (row pitch PP), lattice row gyb (below 2 L) and column gxa +
+// off.
+template <int D, int TX, int TY, int NT, typename E, int PP>
+__device__ __forceinline__ void store_block(const E *lds, int off, int row0, int gxa, int gyb, int L,
+                                            gint32 *__restrict__ hout, int ref)
+{
+    // ---- store the block: aligned 16-byte chunks (LDS and global columns
+    // share their alignment), masked single stores in the partial chunks
+    {
+        constexpr int SPR = (TX * D) / 4;  // chunk slots per row, from the first (maybe partial) one
+        static_assert(NT % SPR == 0, "threads must tile whole block rows");
+        constexpr int RPP = NT / SPR;   // rows per pass of the workgroup
+        const int m = off & 3;
+        const int slot = threadIdx.x % SPR;
+        const int kslot = (off >> 2) + slot;  // LDS chunk index of this thread
+        int gc = gxa + 4 * kslot;
+        if (gc >= L) gc -= L;
+        if (gc >= L) gc -= L;
+        const bool partial = slot == 0 && m != 0;
+        // chunks whose 128-byte line lies wholly inside the block row are
+        // streamed past the caches; lines shared with the neighbouring block
+        // go through L2, where the two halves merge (row bases are
+        // line-aligned when L % 32 == 0)
+        const int row_lo = 4 * (gxa + off), row_hi = row_lo + 4 * (TX * D);
+        const int line = (4 * (gxa + 4 * kslot)) & ~127;
+        const bool whole_line = (L % 32 == 0) && line >= row_lo && line + 128 <= row_hi &&
+                                gxa + off + (TX * D) <= L;
+        // (separate loops: the compiler would otherwise merge the two kinds
+        // of store into one plain store)
+        if (whole_line) {
+            for (int r = threadIdx.x / SPR; r < (TY * D); r += RPP) {
+                int gy = gyb + r;
+                if (gy >= L) gy -= L;
+                const E *src = lds + (row0 + r) * PP + 4 * kslot;
+                store4_stream(hout + (size_t)gy * L + gc,
+                              Lds4<E>::widen(*reinterpret_cast<const typename Lds4<E>::raw *>(src), ref));
+            }
+        } else {
+            for (int r = threadIdx.x / SPR; r < (TY * D); r += RPP) {
+                int gy = gyb + r;
+                if (gy >= L) gy -= L;
+                gint32 *row = hout + (size_t)gy * L;
+                const E *src = lds + (row0 + r) * PP + 4 * kslot;
+                const int4 v = Lds4<E>::widen(*reinterpret_cast<const typename Lds4<E>::raw *>(src), ref);
+                if (!partial) {
+                    store4(row + gc, v);
+                } else {
+                    if (m <= 1) row[gc + 1] = v.y;
+                    if (m <= 2) row[gc + 2] = v.z;
+                    row[gc + 3] = v.w;
+                }
+            }
+        }
+        // the trailing partial chunk of each row (cells 0 .. m-1)
+        if (m != 0) {
+            const int kt = (off >> 2) + SPR;
+            int gct = gxa + 4 * kt;
+            if (gct >= L) gct -= L;
+            if (gct >= L) gct -= L;
+            for (int r = threadIdx.x; r < (TY * D); r += NT) {
+                int gy = gyb + r;
+                if (gy >= L) gy -= L;
+                gint32 *row = hout + (size_t)gy * L;
+                const E *src = lds + (row0 + r) * PP + 4 * kt;
+                row[gct] = ref + (int)src[0];
+                if (m >= 2) row[gct + 1] = ref + (int)src[1];
+                if (m >= 3) row[gct + 2] = ref + (int)src[2];
+            }
+        }
+    }
+}
+
 // ---------------------------------------------------------------------------
 // One region (the TX x TY tiles of the shifted frame at bp) of sweep s, int32 heights in HBM: stage
 // the region and its ring of D+1 sites in LDS, run both phases, store the
@@ -994,80 +1075,20 @@ __device__ __forceinline__ bool region_sweep(E *lds, SurfDev &d, BlockPos bp, lo
     // the block's sums are final: commit them before the stores
     unsigned long long before = 0;
     bool last = false;
-    if (commit_here) before = commit_sweep<NT>(d, b, ca, cs2);
+    if (commit_here) {
+        long long inc[2] = {ca, cs2};
+        before = commit_sweep<NT>(d, b, inc);
+    }
     // Many blocks in flight: better to wait for the count here than for the
     // stores at the block's end, and to start the block's stores together
     // (16 sweeps at L = 16384: 6.63 ms with waves 1..3 ahead, 6.50 ms so).
     if (SCHED != 2 && commit_here) {
-        last = is_last(d, before);
+        last = is_last(d.nblocks, before);
         __syncthreads();
     }
 
-    // ---- store the block: aligned 16-byte chunks (LDS and global columns
-    // share their alignment), masked single stores in the partial chunks
-    {
-        constexpr int SPR = G::BW / 4;  // chunk slots per row, from the first (maybe partial) one
-        static_assert(NT % SPR == 0, "threads must tile whole block rows");
-        constexpr int RPP = NT / SPR;   // rows per pass of the workgroup
-        const int m = off & 3;
-        const int slot = threadIdx.x % SPR;
-        const int kslot = (off >> 2) + slot;  // LDS chunk index of this thread
-        int gc = gxa + 4 * kslot;
-        if (gc >= L) gc -= L;
-        if (gc >= L) gc -= L;
-        const bool partial = slot == 0 && m != 0;
-        // chunks whose 128-byte line lies wholly inside the block row are
-        // streamed past the caches; lines shared with the neighbouring block
-        // go through L2, where the two halves merge (row bases are
-        // line-aligned when L % 32 == 0)
-        const int row_lo = 4 * (gxa + off), row_hi = row_lo + 4 * G::BW;
-        const int line = (4 * (gxa + 4 * kslot)) & ~127;
-        const bool whole_line = (L % 32 == 0) && line >= row_lo && line + 128 <= row_hi &&
-                                gxa + off + G::BW <= L;
-        // (separate loops: the compiler would otherwise merge the two kinds
-        // of store into one plain store)
-        if (whole_line) {
-            for (int r = threadIdx.x / SPR; r < G::BH; r += RPP) {
-                int gy = gy0 + G::RING + r;
-                if (gy >= L) gy -= L;
-                const E *src = lds + (G::RING + r) * PP + 4 * kslot;
-                store4_stream(hout + (size_t)gy * L + gc,
-                              Lds4<E>::widen(*reinterpret_cast<const typename Lds4<E>::raw *>(src), ref));
-            }
-        } else {
-            for (int r = threadIdx.x / SPR; r < G::BH; r += RPP) {
-                int gy = gy0 + G::RING + r;
-                if (gy >= L) gy -= L;
-                gint32 *row = hout + (size_t)gy * L;
-                const E *src = lds + (G::RING + r) * PP + 4 * kslot;
-                const int4 v = Lds4<E>::widen(*reinterpret_cast<const typename Lds4<E>::raw *>(src), ref);
-                if (!partial) {
-                    store4(row + gc, v);
-                } else {
-                    if (m <= 1) row[gc + 1] = v.y;
-                    if (m <= 2) row[gc + 2] = v.z;
-                    row[gc + 3] = v.w;
-                }
-            }
-        }
-        // the trailing partial chunk of each row (cells 0 .. m-1)
-        if (m != 0) {
-            const int kt = (off >> 2) + SPR;
-            int gct = gxa + 4 * kt;
-            if (gct >= L) gct -= L;
-            if (gct >= L) gct -= L;
-            for (int r = threadIdx.x; r < G::BH; r += NT) {
-                int gy = gy0 + G::RING + r;
-                if (gy >= L) gy -= L;
-                gint32 *row = hout + (size_t)gy * L;
-                const E *src = lds + (G::RING + r) * PP + 4 * kt;
-                row[gct] = ref + (int)src[0];
-                if (m >= 2) row[gct + 1] = ref + (int)src[1];
-                if (m >= 3) row[gct + 2] = ref + (int)src[2];
-            }
-        }
-    }
-    if (SCHED == 2 && commit_here) last = is_last(d, before);
+    store_block<D, TX, TY, NT, E, PP>(lds, off, G::RING, gxa, gy0 + G::RING, L, hout, ref);
+    if (SCHED == 2 && commit_here) last = is_last(d.nblocks, before);
     if (last) finish_sweep<false>(d, t);
     return true;
 }
@@ -1126,6 +1147,200 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(
         if constexpr (!std::is_void<EW>::value)
             wide_sweep<D, TX / W::SX, TY / W::SY, NT, EW, SCHED, W::SX, W::SY>((EW *)lds_raw, d, bp, t, ox, oy,
                                                                            &s_bad, ca, cs2, b);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Two sweeps in one pass over the lattice.  A block of the second sweep's
+// frame needs the first sweep's result on itself and RING sites around it:
+// the tiles of the first frame that cover those are (TX + 4) x (TY + 3 or 4)
+// tiles at most, swept in LDS from a region with a ring of its own, as
+// region_sweep does; then the second sweep runs on the same staging, whose
+// tiles lie cx, cy sites further in.  Half the lattice traffic, launches and
+// commits per sweep, for more attempts (1.5 instead of 1.16 per counted one
+// at 32 x 8 tiles).  The first sweep's tiles are counted by the block that
+// holds their corner site.
+//
+// Each launch changes buffers, so a pair of sweeps leaves the state in the
+// buffer of the wrong parity and the next pair brings it back (flip): the
+// host launches this kernel twice, for four sweeps that every surface makes.
+//
+// Host requirements as for region_sweep with the larger region (L at least
+// its rows), 2 N D <= 96 for int8, N (RW + RH + 4) + 2 D^2 <= 32767.
+// Bound by the latency of a launch's parts (start, loads, four dependent
+// phases, commit, stores), which a pair pays once: L = 2048 23.2 -> 18.8 us
+// per sweep, L = 4096 42.4 -> 36.4.  Where every CU is full the attempts are
+// the bound, and L = 16384 takes 406 -> 431 (32 x 16 blocks): not used there.
+// Blocks are full power-of-two workgroups: 12 rows of tiles and 6 waves took
+// 45 us at L = 4096, 16 x 16 tiles and 4.5 waves 60.
+// ---------------------------------------------------------------------------
+constexpr int kTwoMargin = 4;  // more tiles a side in the first sweep
+
+template <int D, int TX, int TY, int NT, typename E, int U = 8>
+__device__ __forceinline__ bool region_sweep2(E *lds, SurfDev &d, BlockPos bp, long long t, uint32_t flip, int ox0,
+                                              int oy0, int ox1, int oy1, int *s_bad, long long (&inc)[4],
+                                              bool commit_here, int b)
+{
+    constexpr int W0 = TX + kTwoMargin;
+    using G = BlockGeom<D, W0, TY + kTwoMargin>;
+    constexpr int RING = G::RING, PP = RowPitch<(int)sizeof(E), G::RWL, 0>::v, LOG2D = TileBits<D>::LOG2D;
+    constexpr bool checked = sizeof(E) == 1;
+    const uint32_t s = (uint32_t)t;
+    const int L = d.L, N = d.N, T = d.T;
+    const uint32_t k0 = d.key0, k1 = d.key1;
+    const gint32 *__restrict__ hin = as_global(d.buf[(s + flip) & 1u]);
+    gint32 *__restrict__ hout = as_global(d.buf[(s + flip + 1u) & 1u]);
+
+    // the block's corner, and the first frame's tile that holds the site RING
+    // up and left of it
+    const int X1 = ox1 + D * bp.tx, Y1 = oy1 + D * bp.ty;
+    const int tx0 = (X1 - RING - ox0) >> LOG2D, ty0 = (Y1 - RING - oy0) >> LOG2D;
+    const int cx = X1 - ox0 - D * tx0, cy = Y1 - oy0 - D * ty0;   // RING .. RING + D - 1
+    const int H0 = (cy + D * TY + RING + D - 1) >> LOG2D;          // TY + 3 or TY + 4
+    int gx0 = X1 - cx - RING, gy0 = Y1 - cy - RING;
+    gx0 = gx0 < 0 ? gx0 + L : gx0 >= L ? gx0 - L : gx0;
+    gy0 = gy0 < 0 ? gy0 + L : gy0 >= L ? gy0 - L : gy0;
+    const int cpad = gx0 & 3, gxa = gx0 - cpad;
+    const int ref = hin[(size_t)gy0 * L + gx0];
+    const int off = RING + cpad;  // LDS column of the first frame's column 0
+
+    int vmin = 0x7FFFFFFF, vmax = -0x7FFFFFFF;
+    {
+        const int nch = G::CH * (D * H0 + 2 * RING);
+        auto fetch = [&](int i) {
+            const int r = i / G::CH, cc = i - r * G::CH;
+            int gy = gy0 + r;
+            if (gy >= L) gy -= L;
+            int gx = gxa + 4 * cc;
+            if (gx >= L) gx -= L;
+            if (gx >= L) gx -= L;
+            return load4(hin + (size_t)gy * L + gx);
+        };
+        auto stage = [&](int i, const int4 &v) {
+            const int r = i / G::CH, cc = i - r * G::CH;
+            lds_put4<E>(lds + r * PP + 4 * cc, v, ref);
+            if (checked) {
+                vmin = min(vmin, min(min(v.x, v.y), min(v.z, v.w)));
+                vmax = max(vmax, max(max(v.x, v.y), max(v.z, v.w)));
+            }
+        };
+        int i0 = threadIdx.x;
+#pragma unroll 1
+        for (; i0 - (int)threadIdx.x + NT * U <= nch; i0 += NT * U) {
+            int4 v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = fetch(i0 + u * NT);
+#pragma unroll
+            for (int u = 0; u < U; ++u) stage(i0 + u * NT, v[u]);
+        }
+        int4 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (i0 + u * NT < nch) v[u] = fetch(i0 + u * NT);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (i0 + u * NT < nch) stage(i0 + u * NT, v[u]);
+    }
+    // (see region_sweep: a sweep raises no site by more than N D)
+    if (checked && (vmin - ref < -128 || (long long)vmax - ref + 2ll * N * D > 127)) *s_bad = 1;
+    __syncthreads();
+    if (checked && *(volatile int *)s_bad) return false;
+
+    {
+        // the first sweep on W0 x H0 tiles; colour 0: (tile + row + par) even
+        const int par = (tx0 + ty0) & 1, HALF = W0 / 2 * H0, P0 = HALF + W0 + H0;
+        const int xlo = D * max(bp.dupx, 0), ylo = D * max(bp.dupy, 0);  // corners counted from here
+        auto id_of = [&](int ltx, int lty) {
+            int gtx = tx0 + ltx, gty = ty0 + lty;
+            gtx = gtx < 0 ? gtx + T : gtx;
+            gty = gty < 0 ? gty + T : gty;
+            gtx = gtx >= T ? gtx - T : gtx;
+            gty = gty >= T ? gty - T : gty;
+            gtx = gtx >= T ? gtx - T : gtx;  // a region that wraps twice
+            return (uint32_t)(gty * T + gtx);
+        };
+        int acc = 0, q = 0;
+        auto tile = [&](int ltx, int lty, uint32_t p, bool mine) {
+            int a = 0, qq = 0;
+            tile_attempts<D, PP, E, int>(lds, (lty * D + RING) * PP + ltx * D + off, id_of(ltx, lty), s, p, N, k0, k1, a, qq);
+            const int dx = D * ltx - cx, dy = D * lty - cy;
+            if (mine && dx >= xlo && dx < D * TX && dy >= ylo && dy < D * TY) {
+                acc += a;
+                q += qq;
+            }
+        };
+        for (int k = threadIdx.x; k < P0; k += NT) {
+            int lty = k / (W0 / 2);
+            int ltx = 2 * (k % (W0 / 2)) + ((lty + par) & 1);
+            if (k >= HALF) {
+                const int g = k - HALF;
+                if (g < W0 / 2) { lty = -1; ltx = 2 * g + ((par + 1) & 1); }
+                else if (g < W0) { lty = H0; ltx = 2 * (g - W0 / 2) + ((par + H0) & 1); }
+                else { lty = g - W0; ltx = ((par + lty) & 1) ? -1 : W0; }
+            }
+            tile(ltx, lty, 0u, k < HALF);
+        }
+        __syncthreads();
+        for (int k = threadIdx.x; k < HALF; k += NT) {
+            const int lty = k / (W0 / 2);
+            tile(2 * (k % (W0 / 2)) + 1 - ((lty + par) & 1), lty, 1u, true);
+        }
+        __syncthreads();
+        inc[0] += acc;
+        inc[1] += 2ll * (long long)q + (long long)acc + 2ll * (long long)ref * acc;
+    }
+    {
+        int acc = 0, q = 0;
+        block_phases<D, TX, TY, NT, PP, E, int>(lds, off + cx + cy * PP, bp, T, s + 1u, N, k0, k1, acc, q);
+        inc[2] += acc;
+        inc[3] += 2ll * (long long)q + (long long)acc + 2ll * (long long)ref * acc;
+    }
+    bool last = false;
+    if (commit_here) {
+        last = is_last(d.nblocks2, commit_sweep<NT, 2>(d, b, inc));
+        __syncthreads();
+    }
+    store_block<D, TX, TY, NT, E, PP>(lds, off + cx, RING + cy, gxa + off + cx >= L ? gxa - L : gxa, gy0 + RING + cy, L,
+                                      hout, ref);
+    if (last) finish_sweep<false, 2>(d, t);
+    return true;
+}
+
+// Two sweeps per launch for every active surface of the descriptor table (see
+// block_sweep); int8 staging, int16 sub-blocks where a block does not fit.
+template <int D, int TX, int TY, int NT>
+__global__ __launch_bounds__(NT) void block_sweep2(SurfDev *__restrict__ descs, int nsurf, const int *__restrict__ owner,
+                                                   int xmode, int xnbx)
+{
+    using G = BlockGeom<D, TX + kTwoMargin, TY + kTwoMargin>;
+    using GS = BlockGeom<D, TX / 2 + kTwoMargin, TY / 2 + kTwoMargin>;
+    constexpr int NB = RowPitch<1, G::RWL, 0>::v * G::RH, WB = GS::RWL * GS::RH * 2;
+    __shared__ __attribute__((aligned(16))) uint8_t lds_raw[NB > WB ? NB : WB];
+    __shared__ int s_bad;
+    if (threadIdx.x == 0) s_bad = 0;
+
+    const int lb = block_map(blockIdx.x, gridDim.x, xmode, xnbx);
+    SurfDev &d = descs[find_surface<true>(descs, nsurf, owner, lb)];
+    const long long t = d.t;
+    const uint32_t flip = (uint32_t)d.flip;
+    const u32x4 org0 = philox4x32_10(0u, 0u, (uint32_t)t, 2u, d.key0, d.key1);
+    const u32x4 org1 = philox4x32_10(0u, 0u, (uint32_t)t + 1u, 2u, d.key0, d.key1);
+    const int ox0 = (int)(org0.v[0] % (2u * D)), oy0 = (int)(org0.v[1] % (2u * D));
+    const int ox1 = (int)(org1.v[0] % (2u * D)), oy1 = (int)(org1.v[1] % (2u * D));
+    const int b = lb - d.block_start2;
+    const BlockPos bp = block_pos<TX, TY>(b % d.nbx2, b / d.nbx2, d.T);
+    long long inc[4] = {0, 0, 0, 0};
+    __syncthreads();  // s_bad cleared
+    if (__builtin_expect(!region_sweep2<D, TX, TY, NT, int8_t>((int8_t *)lds_raw, d, bp, t, flip, ox0, oy0, ox1, oy1,
+                                                               &s_bad, inc, true, b), 0)) {
+#pragma unroll 1
+        for (int i = 0; i < 4; ++i) {
+            const int sx = (i & 1) * (TX / 2), sy = (i >> 1) * (TY / 2);
+            __syncthreads();  // the previous stores have read the LDS
+            region_sweep2<D, TX / 2, TY / 2, NT, int16_t, 4>((int16_t *)lds_raw, d,
+                                                             BlockPos{bp.tx + sx, bp.ty + sy, bp.dupx - sx, bp.dupy - sy}, t,
+                                                             flip, ox0, oy0, ox1, oy1, &s_bad, inc, i == 3, b);
+        }
     }
 }
 
@@ -1298,8 +1513,11 @@ __device__ __forceinline__ bool region_sweep16(E *lds, SurfDev &d, BlockPos bp, 
         ca += acc;
         cs2 += 2ll * (long long)q + (long long)acc + 2ll * base * acc;
     }
-    unsigned long long before = 0;
-    const bool last = commit_here && is_last(d, before = commit_sweep<NT>(d, b, ca, cs2));
+    bool last = false;
+    if (commit_here) {
+        long long inc[2] = {ca, cs2};
+        last = is_last(d.nblocks, commit_sweep<NT>(d, b, inc));
+    }
 
     // ---- store: 16-byte chunks of 8 residues; 16-bit stores in the partial
     // chunks at both ends of each row
