@@ -227,6 +227,8 @@ const Variant *pick_variant(int D, const std::vector<std::pair<int, int>> &LN, b
 // checkerboard, D = 8), each for up to per_cu blocks per CU, in order of the
 // time that a pair takes at that count.  Per sweep, two per launch against
 // one (us):
+//     8 x 8 in steps      L = 256: 11.3 / 13.9, L = 512: 11.5 / 14.2, L = 1024: 12.9 / 17.1
+//                         (without steps, 32 x 8 tiles: 16.5 at 512, 17.0 at 1024)
 //     32 x 8,  1 per CU   L = 1360: 16.7 / 18.8, L = 2048: 18.8 / 23.2, 64 surfaces of 256: 18.9 / 20.7
 //     32 x 16, 1 per CU   L = 2560: 22.8 / 27.4, 8 surfaces of 1024: 23.3 / 28.7
 //     32 x 8,  3 per CU   L = 3072: 32.7 / 34.6
@@ -236,17 +238,19 @@ const Variant *pick_variant(int D, const std::vector<std::pair<int, int>> &LN, b
 // 431 / 406.
 struct Pair {
     int D, TX, TY, NT, per_cu;
+    bool steps;  // attempts in steps
     void (*launch)(dim3, hipStream_t, SurfDev *, int, const int *, int, int);
 };
 
-template <int D, int TX, int TY, int NT>
+template <int D, int TX, int TY, int NT, bool STEPS>
 void launch_pair(dim3 grid, hipStream_t st, SurfDev *d, int n, const int *owner, int xmode, int xnbx)
 {
-    hipLaunchKernelGGL((rsosk::block_sweep2<D, TX, TY, NT>), grid, dim3(NT), 0, st, d, n, owner, xmode, xnbx);
+    hipLaunchKernelGGL((rsosk::block_sweep2<D, TX, TY, NT, STEPS>), grid, dim3(NT), 0, st, d, n, owner, xmode, xnbx);
 }
 
-#define PAIR(D, TX, TY, NT, PER) {D, TX, TY, NT, PER, launch_pair<D, TX, TY, NT>}
-const Pair kPairs[] = {PAIR(8, 32, 8, 256, 1), PAIR(8, 32, 16, 512, 1), PAIR(8, 32, 8, 256, 3), PAIR(8, 32, 16, 512, 2)};
+#define PAIR(D, TX, TY, NT, PER, STEPS) {D, TX, TY, NT, PER, STEPS, launch_pair<D, TX, TY, NT, STEPS>}
+const Pair kPairs[] = {PAIR(8, 8, 8, 512, 1, true), PAIR(8, 32, 8, 256, 1, false), PAIR(8, 32, 16, 512, 1, false),
+                       PAIR(8, 32, 8, 256, 3, false), PAIR(8, 32, 16, 512, 2, false)};
 #undef PAIR
 
 bool pair_fits(const Pair &q, int L, int N)
@@ -255,7 +259,7 @@ bool pair_fits(const Pair &q, int L, int N)
     const int rwl = (rw + 6) & ~3;
     // (as in variant_fits)
     if (L < q.TX * q.D || rh > L || (rwl > L && !(q.TX * q.D == L && rwl <= 2 * L))) return false;
-    return 2ll * N * q.D <= 96 && (long long)N * (rw + rh + 4) + 2 * q.D * q.D <= 32767;
+    return (q.steps || 2ll * N * q.D <= 96) && (long long)N * (rw + rh + 4) + 2 * q.D * q.D <= 32767;
 }
 
 // The shape for two sweeps per launch of surfaces (L, N), or nullptr (also
@@ -263,11 +267,6 @@ bool pair_fits(const Pair &q, int L, int N)
 const Pair *pick_pair(int D, const std::vector<std::pair<int, int>> &LN)
 {
     if (getenv("RSOS_VARIANT")) return nullptr;
-    // Up to one block of 8 x 8 tiles per CU, single sweeps in steps are as
-    // fast or faster (L = 512: 14.3 / 16.5 us, L = 1024: 17.0 / 17.0).
-    long long small = 0;
-    for (auto &ln : LN) small += (long long)blocks_along(ln.first / D, 8) * blocks_along(ln.first / D, 8);
-    if (small <= kCUs) return nullptr;
     for (const Pair &q : kPairs) {
         if (q.D != D) continue;
         bool ok = true;

@@ -1169,14 +1169,130 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(
 // its rows), 2 N D <= 96 for int8, N (RW + RH + 4) + 2 D^2 <= 32767.
 // Bound by the latency of a launch's parts (start, loads, four dependent
 // phases, commit, stores), which a pair pays once: L = 2048 23.2 -> 18.8 us
-// per sweep, L = 4096 42.4 -> 36.4.  Where every CU is full the attempts are
+// per sweep, L = 4096 42.4 -> 36.4; in steps (8 x 8 tiles) L = 256 13.9 ->
+// 11.3, L = 1024 17.1 -> 12.9.  Where every CU is full the attempts are
 // the bound, and L = 16384 takes 406 -> 431 (32 x 16 blocks): not used there.
 // Blocks are full power-of-two workgroups: 12 rows of tiles and 6 waves took
 // 45 us at L = 4096, 16 x 16 tiles and 4.5 waves 60.
 // ---------------------------------------------------------------------------
 constexpr int kTwoMargin = 4;  // more tiles a side in the first sweep
 
-template <int D, int TX, int TY, int NT, typename E, int U = 8>
+// The tiles of the first sweep: W0 x H of frame tiles from (tx0, ty0), of
+// which those of even tile + row + par go first, and the ones around them.
+template <int W0>
+struct FirstFrame {
+    int tx0, ty0, H, par, half, p0;  // tiles of the second phase, of the first
+    __device__ __forceinline__ FirstFrame(int x, int y, int h)
+        : tx0(x), ty0(y), H(h), par((x + y) & 1), half(W0 / 2 * h), p0(half + W0 + h) {}
+
+    __device__ __forceinline__ void tile(int k, uint32_t p, int &ltx, int &lty) const
+    {
+        lty = k / (W0 / 2);
+        ltx = 2 * (k % (W0 / 2)) + ((lty + par + (int)p) & 1);
+        if (p == 0 && k >= half) {
+            const int g = k - half;
+            if (g < W0 / 2) { lty = -1; ltx = 2 * g + ((par + 1) & 1); }
+            else if (g < W0) { lty = H; ltx = 2 * (g - W0 / 2) + ((par + H) & 1); }
+            else { lty = g - W0; ltx = ((par + lty) & 1) ? -1 : W0; }
+        }
+    }
+    __device__ __forceinline__ uint32_t id(int ltx, int lty, int T) const
+    {
+        int gtx = tx0 + ltx, gty = ty0 + lty;
+        gtx = gtx < 0 ? gtx + T : gtx;
+        gty = gty < 0 ? gty + T : gty;
+        gtx = gtx >= T ? gtx - T : gtx;
+        gty = gty >= T ? gty - T : gty;
+        gtx = gtx >= T ? gtx - T : gtx;  // a region that wraps twice
+        return (uint32_t)(gty * T + gtx);
+    }
+};
+
+// The four phases of two sweeps in steps (see BlockSteps, whose tile order
+// the second sweep takes).
+template <int D, int TX, int TY, int NT>
+struct PairSteps {
+    using TB = TileBits<D>;
+    using R = StepList<D>;
+    using G = BlockGeom<D, TX + kTwoMargin, TY + kTwoMargin>;
+    using F = FirstFrame<TX + kTwoMargin>;
+    using Second = BlockSteps<D, TX, TY, NT, G::RWL, G::RH>;
+    static constexpr int P = G::RWL, RING = D + 1;
+    // each phase's first tile in the lists, and first 16 tiles
+    static constexpr int K1 = G::P0, K2 = K1 + G::HALF, K3 = K2 + Second::P0, ALL = K3 + Second::HALF;
+    static constexpr int G1 = (K1 + 15) / 16, G2 = G1 + (G::HALF + 15) / 16, G3 = G2 + Second::G0,
+                         GROUPS = G3 + (Second::HALF + 15) / 16;
+    static constexpr int IDLE = Second::IDLE, LISTS = Second::LISTS;
+    static constexpr int STEPS = LISTS + ALL * D * D * kLdsWin + 8;
+    static constexpr int BYTES = 2 * STEPS + 4 * TB::NCALL * GROUPS;
+
+    static __device__ __forceinline__ void clear(int16_t *lds, int N)
+    {
+        int *steps = (int *)(lds + STEPS);
+        for (int i = threadIdx.x; i < TB::NCALL * GROUPS; i += NT) steps[i] = 0;
+        if (threadIdx.x == 0) {
+            int16_t *c = lds + IDLE + 1 + P;
+            c[0] = 0;
+            c[-1] = c[1] = c[-P] = c[P] = (int16_t)-N;
+        }
+    }
+    static __device__ __forceinline__ uint16_t *list(int16_t *lds, int j, int k, int stride)
+    {
+        return (uint16_t *)(lds + LISTS) + (j * R::NPER * ALL + k * stride) * kLdsWin;
+    }
+    static __device__ __forceinline__ void lay_out(int16_t *lds, int off, const F &f, BlockPos bp, int cx, int cy, int T,
+                                                   uint32_t s, uint32_t k0, uint32_t k1)
+    {
+        int *steps = (int *)(lds + STEPS);
+        for (int i = threadIdx.x; i < ALL * TB::NCALL; i += NT) {
+            const int j = i / ALL, k = i - j * ALL;
+            int ltx, lty, base = off, group;
+            uint32_t id, p;
+            if (k < K2) {
+                p = k >= K1;
+                const int m = p ? k - K1 : k;
+                if (m >= (p ? f.half : f.p0)) continue;  // one row of tiles less
+                f.tile(m, p, ltx, lty);
+                id = f.id(ltx, lty, T);
+                group = (p ? G1 : 0) + m / 16;
+            } else {
+                p = k >= K3;
+                Second::tile(k - K2, ltx, lty);
+                int gtx = bp.tx + ltx, gty = bp.ty + lty;
+                gtx = gtx < 0 ? gtx + T : (gtx >= T ? gtx - T : gtx);
+                gty = gty < 0 ? gty + T : (gty >= T ? gty - T : gty);
+                id = (uint32_t)(gty * T + gtx);
+                base += cx + cy * P;
+                group = p ? G3 + (k - K3) / 16 : G2 + (k - K2) / 16;
+            }
+            const int stride = j == TB::NCALL - 1 ? R::NLAST : R::NPER;
+            const int16_t *above = lds + (lty * D + RING - 1) * P + ltx * D + base;
+            const int n = lay_out_steps<D, P, 0>(list(lds, j, k, stride), stride, above,
+                                                 lds_address(lds + IDLE + 1) * 0x10001u, j, id, k < K2 ? s : s + 1u, p, k0, k1);
+            atomicMax(&steps[j * GROUPS + group], n);
+        }
+    }
+    // phase ph: n tiles from list entry k, groups from g; counted(i) says
+    // whether the i-th counts
+    template <typename C>
+    static __device__ __forceinline__ void phase(int16_t *lds, int k, int g, int n, int N, int &acc, int &q, C counted)
+    {
+        const int *steps = (const int *)(lds + STEPS);
+        for (int i = threadIdx.x / kLdsWin; i < n; i += NT / kLdsWin) {
+            int a = 0, qq = 0;
+#pragma unroll 1
+            for (int j = 0; j < TB::NCALL; ++j) {
+                const int m = __builtin_amdgcn_readfirstlane(steps[j * GROUPS + g + i / 16]);
+                const int stride = j == TB::NCALL - 1 ? R::NLAST : R::NPER;
+                make_steps<P, 0>((const uint32_t *)(list(lds, j, k + i, stride) + (threadIdx.x & (kLdsWin - 1)) * stride), m, N, a, qq);
+            }
+            if (counted(i)) { acc += a; q += qq; }
+        }
+        __syncthreads();
+    }
+};
+
+template <int D, int TX, int TY, int NT, typename E, bool STEPS, int U = 8>
 __device__ __forceinline__ bool region_sweep2(E *lds, SurfDev &d, BlockPos bp, long long t, uint32_t flip, int ox0,
                                               int oy0, int ox1, int oy1, int *s_bad, long long (&inc)[4],
                                               bool commit_here, int b)
@@ -1203,6 +1319,7 @@ __device__ __forceinline__ bool region_sweep2(E *lds, SurfDev &d, BlockPos bp, l
     const int cpad = gx0 & 3, gxa = gx0 - cpad;
     const int ref = hin[(size_t)gy0 * L + gx0];
     const int off = RING + cpad;  // LDS column of the first frame's column 0
+    const FirstFrame<W0> f(tx0, ty0, H0);
 
     int vmin = 0x7FFFFFFF, vmax = -0x7FFFFFFF;
     {
@@ -1237,6 +1354,8 @@ __device__ __forceinline__ bool region_sweep2(E *lds, SurfDev &d, BlockPos bp, l
 #pragma unroll
         for (int u = 0; u < U; ++u)
             if (i0 + u * NT < nch) v[u] = fetch(i0 + u * NT);
+        // (no height is read: the loads are on their way meanwhile)
+        if constexpr (STEPS) PairSteps<D, TX, TY, NT>::lay_out(lds, off, f, bp, cx, cy, T, s, k0, k1);
 #pragma unroll
         for (int u = 0; u < U; ++u)
             if (i0 + u * NT < nch) stage(i0 + u * NT, v[u]);
@@ -1246,76 +1365,81 @@ __device__ __forceinline__ bool region_sweep2(E *lds, SurfDev &d, BlockPos bp, l
     __syncthreads();
     if (checked && *(volatile int *)s_bad) return false;
 
-    {
-        // the first sweep on W0 x H0 tiles; colour 0: (tile + row + par) even
-        const int par = (tx0 + ty0) & 1, HALF = W0 / 2 * H0, P0 = HALF + W0 + H0;
-        const int xlo = D * max(bp.dupx, 0), ylo = D * max(bp.dupy, 0);  // corners counted from here
-        auto id_of = [&](int ltx, int lty) {
-            int gtx = tx0 + ltx, gty = ty0 + lty;
-            gtx = gtx < 0 ? gtx + T : gtx;
-            gty = gty < 0 ? gty + T : gty;
-            gtx = gtx >= T ? gtx - T : gtx;
-            gty = gty >= T ? gty - T : gty;
-            gtx = gtx >= T ? gtx - T : gtx;  // a region that wraps twice
-            return (uint32_t)(gty * T + gtx);
+    // the first sweep; a tile counts where its corner lies in the block
+    const int xlo = D * max(bp.dupx, 0), ylo = D * max(bp.dupy, 0);
+    auto mine = [&](int ltx, int lty) {
+        const int dx = D * ltx - cx, dy = D * lty - cy;
+        return dx >= xlo && dx < D * TX && dy >= ylo && dy < D * TY;
+    };
+    int acc = 0, q = 0;
+    if constexpr (STEPS) {
+        using S = PairSteps<D, TX, TY, NT>;
+        auto counts = [&](int m, uint32_t p) {
+            int ltx, lty;
+            f.tile(m, p, ltx, lty);
+            return (p || m < f.half) && mine(ltx, lty);
         };
-        int acc = 0, q = 0;
-        auto tile = [&](int ltx, int lty, uint32_t p, bool mine) {
-            int a = 0, qq = 0;
-            tile_attempts<D, PP, E, int>(lds, (lty * D + RING) * PP + ltx * D + off, id_of(ltx, lty), s, p, N, k0, k1, a, qq);
-            const int dx = D * ltx - cx, dy = D * lty - cy;
-            if (mine && dx >= xlo && dx < D * TX && dy >= ylo && dy < D * TY) {
+        S::phase(lds, 0, 0, f.p0, N, acc, q, [&](int m) { return counts(m, 0u); });
+        S::phase(lds, S::K1, S::G1, f.half, N, acc, q, [&](int m) { return counts(m, 1u); });
+    } else {
+        auto tile = [&](int m, uint32_t p) {
+            int a = 0, qq = 0, ltx, lty;
+            f.tile(m, p, ltx, lty);
+            tile_attempts<D, PP, E, int>(lds, (lty * D + RING) * PP + ltx * D + off, f.id(ltx, lty, T), s, p, N, k0, k1, a, qq);
+            if ((p || m < f.half) && mine(ltx, lty)) {
                 acc += a;
                 q += qq;
             }
         };
-        for (int k = threadIdx.x; k < P0; k += NT) {
-            int lty = k / (W0 / 2);
-            int ltx = 2 * (k % (W0 / 2)) + ((lty + par) & 1);
-            if (k >= HALF) {
-                const int g = k - HALF;
-                if (g < W0 / 2) { lty = -1; ltx = 2 * g + ((par + 1) & 1); }
-                else if (g < W0) { lty = H0; ltx = 2 * (g - W0 / 2) + ((par + H0) & 1); }
-                else { lty = g - W0; ltx = ((par + lty) & 1) ? -1 : W0; }
-            }
-            tile(ltx, lty, 0u, k < HALF);
-        }
+        for (int m = threadIdx.x; m < f.p0; m += NT) tile(m, 0u);
         __syncthreads();
-        for (int k = threadIdx.x; k < HALF; k += NT) {
-            const int lty = k / (W0 / 2);
-            tile(2 * (k % (W0 / 2)) + 1 - ((lty + par) & 1), lty, 1u, true);
-        }
+        for (int m = threadIdx.x; m < f.half; m += NT) tile(m, 1u);
         __syncthreads();
-        inc[0] += acc;
-        inc[1] += 2ll * (long long)q + (long long)acc + 2ll * (long long)ref * acc;
     }
-    {
-        int acc = 0, q = 0;
+    inc[0] += acc;
+    inc[1] += 2ll * (long long)q + (long long)acc + 2ll * (long long)ref * acc;
+    // the second
+    acc = q = 0;
+    if constexpr (STEPS) {
+        using S = PairSteps<D, TX, TY, NT>;
+        auto counts = [&](int m, int k) {
+            int ltx, lty;
+            S::Second::tile(k, ltx, lty);
+            return m < S::Second::HALF && bp.counts(ltx, lty);
+        };
+        S::phase(lds, S::K2, S::G2, S::Second::P0, N, acc, q, [&](int m) { return counts(m, m); });
+        S::phase(lds, S::K3, S::G3, S::Second::HALF, N, acc, q, [&](int m) { return counts(m, S::Second::P0 + m); });
+    } else {
         block_phases<D, TX, TY, NT, PP, E, int>(lds, off + cx + cy * PP, bp, T, s + 1u, N, k0, k1, acc, q);
-        inc[2] += acc;
-        inc[3] += 2ll * (long long)q + (long long)acc + 2ll * (long long)ref * acc;
     }
+    inc[2] += acc;
+    inc[3] += 2ll * (long long)q + (long long)acc + 2ll * (long long)ref * acc;
     bool last = false;
-    if (commit_here) {
-        last = is_last(d.nblocks2, commit_sweep<NT, 2>(d, b, inc));
+    unsigned long long before = 0;
+    if (commit_here) before = commit_sweep<NT, 2>(d, b, inc);
+    if (commit_here && !STEPS) {
+        last = is_last(d.nblocks2, before);
         __syncthreads();
     }
     store_block<D, TX, TY, NT, E, PP>(lds, off + cx, RING + cy, gxa + off + cx >= L ? gxa - L : gxa, gy0 + RING + cy, L,
                                       hout, ref);
+    if (commit_here && STEPS) last = is_last(d.nblocks2, before);
     if (last) finish_sweep<false, 2>(d, t);
     return true;
 }
 
 // Two sweeps per launch for every active surface of the descriptor table (see
-// block_sweep); int8 staging, int16 sub-blocks where a block does not fit.
-template <int D, int TX, int TY, int NT>
+// block_sweep): int8 staging with int16 sub-blocks where a block does not fit,
+// or attempts in steps on int16 staging.
+template <int D, int TX, int TY, int NT, bool STEPS>
 __global__ __launch_bounds__(NT) void block_sweep2(SurfDev *__restrict__ descs, int nsurf, const int *__restrict__ owner,
                                                    int xmode, int xnbx)
 {
     using G = BlockGeom<D, TX + kTwoMargin, TY + kTwoMargin>;
     using GS = BlockGeom<D, TX / 2 + kTwoMargin, TY / 2 + kTwoMargin>;
     constexpr int NB = RowPitch<1, G::RWL, 0>::v * G::RH, WB = GS::RWL * GS::RH * 2;
-    __shared__ __attribute__((aligned(16))) uint8_t lds_raw[NB > WB ? NB : WB];
+    constexpr int BYTES = STEPS ? PairSteps<D, TX, TY, NT>::BYTES : NB > WB ? NB : WB;
+    __shared__ __attribute__((aligned(16))) uint8_t lds_raw[BYTES];
     __shared__ int s_bad;
     if (threadIdx.x == 0) s_bad = 0;
 
@@ -1330,16 +1454,20 @@ __global__ __launch_bounds__(NT) void block_sweep2(SurfDev *__restrict__ descs, 
     const int b = lb - d.block_start2;
     const BlockPos bp = block_pos<TX, TY>(b % d.nbx2, b / d.nbx2, d.T);
     long long inc[4] = {0, 0, 0, 0};
-    __syncthreads();  // s_bad cleared
-    if (__builtin_expect(!region_sweep2<D, TX, TY, NT, int8_t>((int8_t *)lds_raw, d, bp, t, flip, ox0, oy0, ox1, oy1,
-                                                               &s_bad, inc, true, b), 0)) {
+    if constexpr (STEPS) PairSteps<D, TX, TY, NT>::clear((int16_t *)lds_raw, d.N);
+    __syncthreads();  // s_bad (and the counts of steps) cleared
+    if constexpr (STEPS) {
+        region_sweep2<D, TX, TY, NT, int16_t, true>((int16_t *)lds_raw, d, bp, t, flip, ox0, oy0, ox1, oy1, &s_bad, inc,
+                                                    true, b);
+    } else if (__builtin_expect(!region_sweep2<D, TX, TY, NT, int8_t, false>((int8_t *)lds_raw, d, bp, t, flip, ox0, oy0,
+                                                                            ox1, oy1, &s_bad, inc, true, b), 0)) {
 #pragma unroll 1
         for (int i = 0; i < 4; ++i) {
             const int sx = (i & 1) * (TX / 2), sy = (i >> 1) * (TY / 2);
             __syncthreads();  // the previous stores have read the LDS
-            region_sweep2<D, TX / 2, TY / 2, NT, int16_t, 4>((int16_t *)lds_raw, d,
-                                                             BlockPos{bp.tx + sx, bp.ty + sy, bp.dupx - sx, bp.dupy - sy}, t,
-                                                             flip, ox0, oy0, ox1, oy1, &s_bad, inc, i == 3, b);
+            region_sweep2<D, TX / 2, TY / 2, NT, int16_t, false, 4>((int16_t *)lds_raw, d,
+                                                                    BlockPos{bp.tx + sx, bp.ty + sy, bp.dupx - sx, bp.dupy - sy},
+                                                                    t, flip, ox0, oy0, ox1, oy1, &s_bad, inc, i == 3, b);
         }
     }
 }

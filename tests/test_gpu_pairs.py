@@ -30,6 +30,9 @@ def _check(oracle, s_log, s_h, h0, L, N, seed, t0, n, what):
 
 
 @pytest.mark.parametrize("L,N,start,t0,calls", [
+    (256, 1, "flat", 0, (5, 4, 1)),    # 8 x 8 tiles in steps
+    (272, 3, "rough", 1, (70,)),       # blocks that overlap, T = 34
+    (1024, 40, "cone", 0, (7,)),
     (1360, 2, "rough", 0, (4, 7)),     # 32 x 8 tiles, one block per CU
     (1296, 1, "flat", 3, (11,)),       # an odd start time
     (1296, 6, "rough", 0, (9,)),       # the largest N of the byte staging
@@ -50,7 +53,7 @@ def test_pairs(rsos, oracle, L, N, start, t0, calls):
     s.close()
 
 
-@pytest.mark.parametrize("L,copies", [(256, 64), (256, 66), (320, 40), (512, 16)])
+@pytest.mark.parametrize("L,copies", [(256, 16), (256, 64), (256, 66), (320, 40), (512, 16)])
 def test_pairs_batch(rsos, oracle, L, copies):
     """Equal and unequal numbers of sweeps, replayed graphs included."""
     import torch
