@@ -47,6 +47,7 @@ namespace {
 constexpr int kLdsMaxBytes = 64 * 1024;  // surfaces of at most this many bytes of int32 run whole in LDS
 constexpr int kGraphSweeps = 32;
 constexpr long long kNoEnd = 0x7FFFFFFFFFFFFFFFll;  // t_end of a surface with no bound
+constexpr long long kBesideSweeps = 4;  // least sweeps for which a batch's LDS path takes a stream of its own
 constexpr int kCUs = 256;           // of an MI355X
 constexpr int kPsGrid = 2048;       // workgroups of the power-sum reduction
 constexpr size_t kStagingBytes = 4096;      // least size of a pinned staging buffer
@@ -484,6 +485,11 @@ struct SurfaceGroup {
     int graph_k = kGraphSweeps;        // sweeps per captured graph
     size_t lds_bytes = 0;
     bool lds_is_wide = false;
+    // groups with surfaces on both paths: the LDS path's launch runs beside
+    // the tile blocks on a stream of its own, forked from the group's stream
+    // and joined to it within the call
+    hipStream_t lds_stream = nullptr;
+    hipEvent_t fork = nullptr, join = nullptr;
     Staging staging;
     bool pairs = true;                 // two sweeps may share a launch
     bool any_pair = false;             // and do, in some shape
@@ -612,6 +618,11 @@ struct SurfaceGroup {
             std::vector<std::pair<int, int>> ln;
             for (int i : lds_idx) ln.push_back({host[i].L, host[i].N});
             lds_plan(D, sched, ln, &lds_is_wide, &lds_bytes);
+            if (!blk_idx.empty()) {
+                HIP_TRY(hipStreamCreateWithFlags(&lds_stream, hipStreamNonBlocking));
+                HIP_TRY(hipEventCreateWithFlags(&fork, hipEventDisableTiming));
+                HIP_TRY(hipEventCreateWithFlags(&join, hipEventDisableTiming));
+            }
         }
         return upload_all();
     }
@@ -653,18 +664,32 @@ struct SurfaceGroup {
     rsos_status launch_sweeps(long long n)
     {
         if (n <= 0) return RSOS_OK;
+        // Beside the blocks from kBesideSweeps sweeps on: the fork and the join
+        // cost about 10 us (2 surfaces of 64 and 256, one sweep 42 -> 55 us),
+        // four sweeps take 92 -> 82 us and 64 sweeps 1165 -> 753, 300 surfaces
+        // of 64 beside one of 2048 163 -> 128 and 2069 -> 1366.
+        // (Where the runtime puts both streams on one hardware queue, 1 of the
+        // 12 measured, they run in turn and 304 us become 325.)
+        const bool beside = lds_stream && n >= kBesideSweeps;
         if (!lds_idx.empty()) {
-            lds_launcher(D, sched)(dim3((unsigned)lds_idx.size()), lds_bytes, lds_is_wide, stream, d_desc, d_lds_idx);
+            if (beside) {
+                HIP_TRY(hipEventRecord(fork, stream));
+                HIP_TRY(hipStreamWaitEvent(lds_stream, fork, 0));
+            }
+            lds_launcher(D, sched)(dim3((unsigned)lds_idx.size()), lds_bytes, lds_is_wide, beside ? lds_stream : stream,
+                                   d_desc, d_lds_idx);
             HIP_TRY(hipGetLastError());
+            if (beside) HIP_TRY(hipEventRecord(join, lds_stream));
         }
         if (blk_idx.empty()) return RSOS_OK;
         // sweeps that every block-path surface makes: only these may be
         // launched two at a time
         long long every = n;
-        for (int i : blk_idx) every = std::min(every, host[i].t_end - host[i].t);
-        if (!any_pair) every = n;
+        if (any_pair)
+            for (int i : blk_idx) every = std::min(every, host[i].t_end - host[i].t);
         rsos_status st = run_block(every, &graph, any_pair);
         if (st == RSOS_OK) st = run_block(n - every, &graph1, false);
+        if (beside) HIP_TRY(hipStreamWaitEvent(stream, join, 0));
         return st;
     }
 
@@ -928,6 +953,12 @@ struct SurfaceGroup {
     {
         if (stream) (void)hipStreamSynchronize(stream);
         else (void)hipDeviceSynchronize();
+        if (lds_stream) {
+            (void)hipStreamSynchronize(lds_stream);
+            (void)hipStreamDestroy(lds_stream);
+        }
+        if (fork) (void)hipEventDestroy(fork);
+        if (join) (void)hipEventDestroy(join);
         clear_timing();
         if (graph) (void)hipGraphExecDestroy(graph);
         if (graph1) (void)hipGraphExecDestroy(graph1);
