@@ -1757,6 +1757,21 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WideOcc<D, T
                                                                      &s_bad, ca, cs2, b);
 }
 
+// Zeroes up to kFills ranges of whole 16-byte words (one per blockIdx.y), by
+// one launch: a fill call each leaves the stream idle between the fills
+// (24 jobs admitted and run: 3445 -> 3309 us).
+constexpr int kFills = 32;
+struct FillList {
+    int4 *p[kFills];
+    int n16[kFills];
+};
+__global__ void zero_ranges(FillList f)
+{
+    int4 *p = f.p[blockIdx.y];
+    const int n = f.n16[blockIdx.y];
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) p[i] = make_int4(0, 0, 0, 0);
+}
+
 // The record (S1, S2, A) of every surface's current time: out[3 k] for row k
 // of the descriptor table.
 __global__ void gather_records(const SurfDev *__restrict__ descs, int n, long long *__restrict__ out)
