@@ -2,9 +2,11 @@
 //
 // Launch plan per sweep: one block_sweep launch over every tile block of
 // every active surface (the last block of each surface also folds its
-// exact sums into the per-sweep log).  The kernel reads the surface time t
-// from device memory, so a captured hipGraph of K sweeps replays for any t.  Surfaces whose L^2 int32 fit in LDS run all
-// their sweeps in one lds_run launch instead.
+// exact sums into the per-sweep log), or, where a launch's latency is the
+// bound, one block_sweep2 launch for two sweeps.  The kernels read the
+// surface time t from device memory, so a captured hipGraph of K sweeps
+// replays for any t.  Surfaces whose L^2 int32 fit in LDS run all their
+// sweeps in one lds_run launch instead.
 #include "rsos.h"
 #include "rsos_host.hpp"
 #include "rsos_kernels.hpp"

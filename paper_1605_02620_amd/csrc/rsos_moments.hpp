@@ -22,9 +22,11 @@ namespace rsosk {
 // most 2^16 sites per thread) and the rare others in int128.  Workgroup
 // totals go to part[4 * blockIdx.x + k], and power_sums_final adds them into
 // out[0..3] and puts the record behind them, so that one copy brings both.
-// One read of the lattice, kUnroll 16-byte loads in flight per thread: 17.7
-// -> 16.4 us at L = 4096 (64 MiB), of a call of 35 us (58 us with two
-// synchronous copies).  With 16-bit storage R is also
+// One read of the lattice, bound by it: 8192 consecutive sites of a workgroup
+// in flight at a time.  A call (us): L = 4096 57 -> 33 (two synchronous
+// copies were 20 of them), L = 16384 216 -> 202, with 16-bit storage 152 ->
+// 118.  (With each thread's loads a grid apart L = 16384 took 240: eight
+// streams 8 MiB apart.)  With 16-bit storage R is also
 // the reference the residues are decoded against (floor(S1 / L^2) of the
 // same time), so h - R = int16(r - R mod 2^16).
 // ---------------------------------------------------------------------------
@@ -103,9 +105,9 @@ __global__ __launch_bounds__(256) void power_sums_partial(const S *__restrict__ 
     const long long R = rec[0] / n;
     PowerAcc acc;
     constexpr int CPC = 16 / sizeof(S);
-    const long long nch = n / CPC, step = (long long)gridDim.x * 256;
+    const long long nch = n / CPC;
     const int Rl = (int)R;  // |h - R| fits int32: the wrapping difference is exact
-    constexpr int kUnroll = 8;
+    constexpr int kUnroll = sizeof(S) == 4 ? 8 : 4;  // 8192 sites of a workgroup at a time
     auto take = [&](const v4u &v) {
         if constexpr (sizeof(S) == 4) {
             acc.add4((int)(v.x - (uint32_t)Rl), (int)(v.y - (uint32_t)Rl), (int)(v.z - (uint32_t)Rl), (int)(v.w - (uint32_t)Rl));
@@ -117,15 +119,16 @@ __global__ __launch_bounds__(256) void power_sums_partial(const S *__restrict__ 
         }
     };
     const gv4u *src = (const gv4u *)h;
-    long long c = (long long)blockIdx.x * 256 + threadIdx.x;
-    for (; c + (kUnroll - 1) * step < nch; c += kUnroll * step) {
+    // each workgroup's loads in flight are of consecutive chunks
+    long long c = (long long)blockIdx.x * (256 * kUnroll) + threadIdx.x;
+    for (; c + (kUnroll - 1) * 256 < nch; c += (long long)gridDim.x * (256 * kUnroll)) {
         v4u v[kUnroll];
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) v[u] = src[c + u * step];
+        for (int u = 0; u < kUnroll; ++u) v[u] = src[c + u * 256];
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) take(v[u]);
     }
-    for (; c < nch; c += step) {
+    for (; c < nch; c += 256) {
         const v4u v = src[c];
         take(v);
     }
