@@ -309,13 +309,13 @@ rsos_status check_packed(const rsos_params *p)
 }
 
 // Surfaces that live in LDS: lds_run, or lds_run32 (wide) where a
-// restriction of the launch exceeds the 16-bit staging.
+// restriction of the launch exceeds the 16-bit staging, and for many small tiles.
 typedef void (*LdsLaunch)(dim3, size_t, bool, hipStream_t, SurfDev *, const int *);
 template <int D, int SCHED>
 void launch_lds(dim3 grid, size_t shm, bool wide, hipStream_t st, SurfDev *d, const int *w)
 {
     if (wide) hipLaunchKernelGGL((rsosk::lds_run32<D, 256, SCHED>), grid, dim3(256), shm, st, d, w);
-    else hipLaunchKernelGGL((rsosk::lds_run<D, rsosk::kLdsThreads, SCHED>), grid, dim3(rsosk::kLdsThreads), shm, st, d, w);
+    else if constexpr (D > 2) hipLaunchKernelGGL((rsosk::lds_run<D, rsosk::kLdsThreads, SCHED>), grid, dim3(rsosk::kLdsThreads), shm, st, d, w);
 }
 LdsLaunch lds_launcher(int D, int sched = 0)
 {
@@ -336,7 +336,15 @@ LdsLaunch lds_launcher(int D, int sched = 0)
     return nullptr;
 }
 
-bool lds_wide(int L, int N) { return (long long)N * L > rsosk::kLdsRunMaxNL; }
+// The steps are for few tiles with long chains of attempts: where small tiles
+// fill the lanes, one lane each does better (us per sweep, steps / one lane:
+// D = 2, L = 32: 3.6 / 3.2, L = 128: 21.0 / 15.2; D = 4, L = 16: 4.0 / 5.8,
+// L = 32: 4.2 / 6.0, L = 64: 7.2 / 6.7, L = 128: 19.0 / 13.2; D = 8, L = 128:
+// 14.6 / 24.2).
+bool lds_wide(int D, int L, int N)
+{
+    return D == 2 || (D == 4 && L > 32) || (long long)N * L > rsosk::kLdsRunMaxNL;
+}
 
 // LDS of one workgroup that runs a surface of side L.
 size_t lds_bytes_of(int D, int sched, int L, bool wide)
@@ -344,7 +352,6 @@ size_t lds_bytes_of(int D, int sched, int L, bool wide)
     if (wide) return (size_t)L * L * 4;
     const int ph = sched == 1 ? 4 : 2;
     switch (D) {
-    case 2: return (size_t)rsosk::LdsRun<2>::bytes(L, ph);
     case 4: return (size_t)rsosk::LdsRun<4>::bytes(L, ph);
     case 8: return (size_t)rsosk::LdsRun<8>::bytes(L, ph);
     case 16: return (size_t)rsosk::LdsRun<16>::bytes(L, ph);
@@ -357,7 +364,7 @@ size_t lds_bytes_of(int D, int sched, int L, bool wide)
 void lds_plan(int D, int sched, const std::vector<std::pair<int, int>> &LN, bool *wide, size_t *bytes)
 {
     *wide = false;
-    for (auto &x : LN) *wide = *wide || lds_wide(x.first, x.second);
+    for (auto &x : LN) *wide = *wide || lds_wide(D, x.first, x.second);
     *bytes = 0;
     for (auto &x : LN) *bytes = std::max(*bytes, lds_bytes_of(D, sched, x.first, *wide));
 }

@@ -2086,8 +2086,8 @@ __global__ __launch_bounds__(NT) void lds_run(SurfDev *__restrict__ descs, const
 
 // ---------------------------------------------------------------------------
 // lds_run32: the same for restrictions with N L > kLdsRunMaxNL (up to none at
-// all): int32 heights on the bare torus, one lane per tile, the LDS is
-// L_max^2 int32.
+// all) and for small tiles that fill the lanes: int32 heights on the bare
+// torus, one lane per tile, the LDS is L_max^2 int32.
 // ---------------------------------------------------------------------------
 template <int D>
 __device__ __forceinline__ int tile_attempts_torus(int32_t *h, int L, int x0, int y0,
