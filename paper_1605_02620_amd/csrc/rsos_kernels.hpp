@@ -1928,12 +1928,24 @@ __global__ __launch_bounds__(NT) void lds_run(SurfDev *__restrict__ descs, const
     int ox, oy;
     origin(t, ox, oy);
     int base;
+    // thread 0 keeps the sums, from those of the lattice itself (the record
+    // of the start may be a caller's)
+    __shared__ long long s_start[2][NT / 64];
+    long long S1 = 0, S2 = 0, slot = d.slot;
     {
         const int32_t *src = d.buf[t & 1];
         base = src[0];
         for (int i = tid; i < L * L; i += NT) {
-            const int y = i / L, x = i - y * L;
-            h[(y < oy ? y + L : y) * P + (x < ox ? x + L : x)] = (int16_t)(src[i] - base);
+            const int y = i / L, x = i - y * L, v = src[i];
+            h[(y < oy ? y + L : y) * P + (x < ox ? x + L : x)] = (int16_t)(v - base);
+            S1 += v;
+            S2 += (long long)v * v;
+        }
+        S1 = wave_sum63_64(S1);
+        S2 = wave_sum63_64(S2);
+        if ((tid & 63) == 63) {
+            s_start[0][tid >> 6] = S1;
+            s_start[1][tid >> 6] = S2;
         }
         for (int i = tid; i < 2 * TB::NCALL * GROUPS; i += NT) (&s_steps[0][0][0])[i] = 0;
         if (tid < 4) s_sum[tid >> 1][tid & 1] = 0;
@@ -1942,14 +1954,14 @@ __global__ __launch_bounds__(NT) void lds_run(SurfDev *__restrict__ descs, const
             idle[-1] = idle[1] = idle[-P] = idle[P] = (int16_t)-N;
         }
     }
-    // thread 0 keeps the sums
-    long long S1 = 0, S2 = 0, slot = d.slot;
-    if (tid == 0) {
-        const long long *rec = d.log + 3 * slot;
-        S1 = rec[0];
-        S2 = rec[1];
-    }
     __syncthreads();
+    if (tid == 0) {
+        S1 = S2 = 0;
+        for (int w = 0; w < NT / 64; ++w) {
+            S1 += s_start[0][w];
+            S2 += s_start[1][w];
+        }
+    }
 
     const float r_half = 1.0f / (float)(T / 2), r_tiles = 1.0f / (float)ntiles, r_all = 1.0f / (float)all;
     // tile k of phase p: its place in the window, in tiles

@@ -73,3 +73,29 @@ def test_mixed_launch(rsos, oracle):
             r_h, r_log = _oracle(oracle, workloads.flat(L), L, N, 8, seed, 3 + i)
             _same(b.log(i, 1, 3 + i), r_log, b.heights(i), r_h, f"surface {i}")
         b.close()
+
+
+@pytest.mark.parametrize("L,N,D,schedule", [(64, 1, 8, "checkerboard"), (128, 3, 16, "double"),
+                                            (128, 100, 8, "checkerboard")])
+def test_sums_are_the_lattice_s_own(rsos, oracle, L, N, D, schedule):
+    """rsos_sweep_static: the records of an LDS-resident surface are sums of
+    its heights, whatever sums of the start the caller passes."""
+    import ctypes
+
+    import torch
+    from paper_1605_02620_amd import _lib
+    from paper_1605_02620_amd.surface import _params
+    print(f"[lds] sums L={L} N={N} D={D} {schedule}", flush=True)
+    n, h0 = 5, workloads.rough(L, min(N, 64), seed=L + N, base=1000)
+    r_h, r_log = _oracle(oracle, h0, L, N, D, 9, n, schedule)
+    s1, s2 = int(h0.astype(np.int64).sum()), int((h0.astype(np.int64) ** 2).sum())
+    for sums in ((s1, s2), (0, 0), (s1 + 7, 2 * s2)):
+        bufs = [torch.from_numpy(h0.astype(np.int32)).cuda(), torch.zeros(L * L, dtype=torch.int32, device="cuda")]
+        log = torch.zeros(3 * n, dtype=torch.int64, device="cuda")
+        p = _params(L, N, D, 9, schedule=schedule)
+        _lib.check(_lib.lib().rsos_sweep_static(
+            ctypes.byref(p), ctypes.c_void_p(bufs[0].data_ptr()), ctypes.c_void_p(bufs[1].data_ptr()), 0, *sums, n,
+            ctypes.c_void_p(log.data_ptr()), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)))
+        torch.cuda.synchronize()
+        assert np.array_equal(log.cpu().numpy().reshape(n, 3), r_log[:, 1:4]), f"sums given as {sums}"
+        assert np.array_equal(bufs[n & 1].cpu().numpy(), r_h)
