@@ -17,6 +17,7 @@
 #include <hip/hip_ext.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -51,6 +52,7 @@ constexpr int kGraphSweeps = 32;
 constexpr long long kNoEnd = 0x7FFFFFFFFFFFFFFFll;  // t_end of a surface with no bound
 constexpr long long kBesideSweeps = 4;  // least sweeps for which a batch's LDS path takes a stream of its own
 constexpr int kCUs = 256;           // of an MI355X
+constexpr size_t kLdsOfCU = 160 * 1024, kLdsStatic = 1024;  // LDS of a CU; of an LDS-path kernel's static arrays, at most about
 constexpr int kPsGrid = 2048;       // workgroups of the power-sum reduction
 constexpr size_t kStagingBytes = 4096;      // least size of a pinned staging buffer
 constexpr long long kReadRecords = 1 << 15; // most log records copied at once (768 KiB pinned)
@@ -308,14 +310,23 @@ rsos_status check_packed(const rsos_params *p)
     return RSOS_OK;
 }
 
-// Surfaces that live in LDS: lds_run, or lds_run32 (wide) where a
-// restriction of the launch exceeds the 16-bit staging, and for many small tiles.
-typedef void (*LdsLaunch)(dim3, size_t, bool, hipStream_t, SurfDev *, const int *);
+// How a launch runs surfaces that live in LDS: attempts in steps (lds_run),
+// with the next sweep's steps laid out ahead where that is offered or with
+// one phase's at a time, or one lane per tile (lds_run32).
+enum class LdsMode { kAhead, kSteps, kLane };
+struct LdsPlan {
+    LdsMode mode = LdsMode::kLane;
+    size_t bytes = 0;  // of dynamic LDS per workgroup
+};
+typedef void (*LdsLaunch)(dim3, const LdsPlan &, hipStream_t, SurfDev *, const int *);
 template <int D, int SCHED>
-void launch_lds(dim3 grid, size_t shm, bool wide, hipStream_t st, SurfDev *d, const int *w)
+void launch_lds(dim3 grid, const LdsPlan &pl, hipStream_t st, SurfDev *d, const int *w)
 {
-    if (wide) hipLaunchKernelGGL((rsosk::lds_run32<D, 256, SCHED>), grid, dim3(256), shm, st, d, w);
-    else if constexpr (D > 2) hipLaunchKernelGGL((rsosk::lds_run<D, rsosk::kLdsThreads, SCHED>), grid, dim3(rsosk::kLdsThreads), shm, st, d, w);
+    if (pl.mode == LdsMode::kLane)
+        hipLaunchKernelGGL((rsosk::lds_run32<D, 256, SCHED>), grid, dim3(256), pl.bytes, st, d, w);
+    else if constexpr (D > 2)
+        hipLaunchKernelGGL((rsosk::lds_run<D, rsosk::kLdsThreads, SCHED>), grid, dim3(rsosk::kLdsThreads), pl.bytes, st, d, w,
+                           pl.mode == LdsMode::kAhead ? 1 : 0);
 }
 LdsLaunch lds_launcher(int D, int sched = 0)
 {
@@ -347,26 +358,93 @@ bool lds_wide(int D, int L, int N)
 }
 
 // LDS of one workgroup that runs a surface of side L.
-size_t lds_bytes_of(int D, int sched, int L, bool wide)
+size_t lds_bytes_of(int D, int sched, int L, LdsMode mode)
 {
-    if (wide) return (size_t)L * L * 4;
+    if (mode == LdsMode::kLane) return (size_t)L * L * 4;
     const int ph = sched == 1 ? 4 : 2;
+    auto bytes = [&](auto run) -> size_t {
+        using R = decltype(run);
+        return (size_t)R::bytes(L, ph, mode == LdsMode::kAhead && R::ahead(L, ph));
+    };
     switch (D) {
-    case 4: return (size_t)rsosk::LdsRun<4>::bytes(L, ph);
-    case 8: return (size_t)rsosk::LdsRun<8>::bytes(L, ph);
-    case 16: return (size_t)rsosk::LdsRun<16>::bytes(L, ph);
+    case 4: return bytes(rsosk::LdsRun<4>());
+    case 8: return bytes(rsosk::LdsRun<8>());
+    case 16: return bytes(rsosk::LdsRun<16>());
     }
-    return (size_t)rsosk::LdsRun<32>::bytes(L, ph);
+    return bytes(rsosk::LdsRun<32>());
 }
 
-// The (L, N) of the surfaces of one launch: whether it takes the wide
-// kernel, and the LDS of its workgroups.
-void lds_plan(int D, int sched, const std::vector<std::pair<int, int>> &LN, bool *wide, size_t *bytes)
+// What a sweep of one surface takes alone on its CU, by mode (us; columns:
+// L up to 64, 80, 96, 112, 128), and the workgroups per CU that the registers
+// allow.  Measured with 256 surfaces of one size per launch.
+struct LdsCost {
+    int D, sched, steps_per_cu, lane_per_cu;
+    float ahead, steps[5], lane[5];
+};
+const LdsCost kLdsCosts[] = {
+    {4, 0, 2, 4, 4.6f, {6.2f, 6.2f, 6.2f, 6.2f, 6.2f}, {6.6f, 6.6f, 6.6f, 6.6f, 6.6f}},  // (in steps up to L = 32 only)
+    {8, 0, 3, 8, 7.6f, {10.5f, 11.4f, 12.3f, 14.5f, 15.9f}, {23.f, 21.6f, 25.5f, 25.8f, 26.8f}},
+    {8, 1, 3, 8, 12.3f, {17.8f, 18.7f, 19.3f, 20.3f, 20.9f}, {45.f, 45.f, 40.f, 42.f, 43.f}},
+    {16, 0, 2, 4, 19.f, {20.f, 23.f, 25.8f, 28.f, 29.9f}, {76.f, 76.f, 76.f, 76.f, 76.f}},
+    {16, 1, 2, 4, 32.f, {34.f, 36.f, 38.4f, 42.f, 45.f}, {152.f, 152.f, 152.f, 152.f, 152.f}},
+    {32, 0, 3, 8, 70.f, {71.f, 72.f, 73.f, 73.f, 74.f}, {355.f, 355.f, 355.f, 355.f, 355.f}},
+};
+
+// The plan of one launch of surfaces (L, N): the mode with the least time by
+// the table.  A workgroup makes all its sweeps before the next takes its
+// place, so beyond what is resident at once the launch takes rounds (a last
+// one with fewer workgroups per CU is the shorter), and one of several
+// workgroups per CU takes c times as long.  The
+// steps are the shorter chain, but need more LDS and registers: with the
+// lists of two sweeps (ahead) 90 KB at L = 64, one workgroup per CU, with one
+// phase's 41 KB, three, with one lane per tile 16 KB, eight.  Measured, us per
+// sweep of the launch (ahead / steps / one lane; D = 8):
+//     L = 32:  n = 256 7.4 / 10.2 / 23.0, 1024 14.4 / 20.1 / 25.4, 4096 43 / 58 / 58
+//     L = 64:  n = 256 8.2 / 10.7 / 22.9, 768 22.5 / 14.1 / 23.3, 1024 29.2 / 22.0 / 23.5, 2048 57 / 37 / 32, 4096 114 / 68 / 60
+//     L = 80:  n = 768 - / 23.2 / 24.7, 1024 - / 27.3 / 25.1, 4096 - / 101 / 77
+//     L = 112: n = 512 - / 27.8 / 31.7, 768 - / 41.5 / 33.3, 4096 - / 211 / 163
+//     L = 128: n = 256 - / 15.9 / 26.9, 1024 - / 58.5 / 62.5, 4096 - / 231 / 232
+//     n each of L = 32 and 64: 342 21.5 / 13.6 / 24.4, 1024 54.5 / 33.6 / 31.6
+//     n each of L = 32, 64, 128: 1024 112 / 133 / 157
+// and D = 16, L = 64, n = 1024: 79 / 45 / 98, D = 4, L = 32: n = 512 5.9 / 7.2 / 7.4, 1024 10.5 / 13.2 / 8.9.
+LdsPlan lds_plan(int D, int sched, const std::vector<std::pair<int, int>> &LN)
 {
-    *wide = false;
-    for (auto &x : LN) *wide = *wide || lds_wide(D, x.first, x.second);
-    *bytes = 0;
-    for (auto &x : LN) *bytes = std::max(*bytes, lds_bytes_of(D, sched, x.first, *wide));
+    const LdsCost *cost = nullptr;
+    for (const LdsCost &c : kLdsCosts)
+        if (c.D == D && c.sched == sched) cost = &c;
+    for (auto &x : LN)
+        if (lds_wide(D, x.first, x.second)) cost = nullptr;
+    LdsPlan best;
+    double best_time = 0.0;
+    for (LdsMode mode : {LdsMode::kAhead, LdsMode::kSteps, LdsMode::kLane}) {
+        if (!cost && mode != LdsMode::kLane) continue;  // one lane per tile only
+        LdsPlan pl;
+        pl.mode = mode;
+        double sum = 0.0, most = 0.0;
+        bool ahead = true;
+        for (auto &x : LN) {
+            ahead = ahead && x.first <= 64;
+            pl.bytes = std::max(pl.bytes, lds_bytes_of(D, sched, x.first, mode));
+            if (!cost) continue;
+            const int col = x.first <= 64 ? 0 : std::min((x.first - 49) / 16, 4);
+            const double t = mode == LdsMode::kLane ? cost->lane[col]
+                             : mode == LdsMode::kAhead && x.first <= 64 ? cost->ahead : cost->steps[col];
+            sum += t;
+            most = std::max(most, t);
+        }
+        if (!cost) return pl;
+        const int fit = std::max(1, std::min((int)(kLdsOfCU / (pl.bytes + kLdsStatic)),
+                                             mode == LdsMode::kLane ? cost->lane_per_cu : cost->steps_per_cu));
+        const int per_cu = ((int)LN.size() + kCUs - 1) / kCUs, here = std::min(fit, per_cu);
+        const double load = (double)per_cu / fit, rounds = std::max(1.0, (std::ceil(load) + load) / 2);
+        const double c = here == 1 ? 1.0 : mode == LdsMode::kAhead && here == 2 && ahead ? 1.12 : here == 2 ? 1.25 : 1.3;
+        const double time = std::max(most, sum / LN.size() * rounds) * c;
+        if (best.bytes == 0 || time < best_time) {
+            best = pl;
+            best_time = time;
+        }
+    }
+    return best;
 }
 
 bool valid_D(int D) { return D == 2 || D == 4 || D == 8 || D == 16 || D == 32; }
@@ -492,8 +570,7 @@ struct SurfaceGroup {
     std::vector<int> lds_idx, blk_idx; // surfaces on each path
     int *d_lds_idx = nullptr;
     int graph_k = kGraphSweeps;        // sweeps per captured graph
-    size_t lds_bytes = 0;
-    bool lds_is_wide = false;
+    LdsPlan lds;
     // groups with surfaces on both paths: the LDS path's launch runs beside
     // the tile blocks on a stream of its own, forked from the group's stream
     // and joined to it within the call
@@ -626,7 +703,7 @@ struct SurfaceGroup {
             HIP_TRY(hipMemcpy(d_lds_idx, pos.data(), sizeof(int) * pos.size(), hipMemcpyHostToDevice));
             std::vector<std::pair<int, int>> ln;
             for (int i : lds_idx) ln.push_back({host[i].L, host[i].N});
-            lds_plan(D, sched, ln, &lds_is_wide, &lds_bytes);
+            lds = lds_plan(D, sched, ln);
             if (!blk_idx.empty()) {
                 HIP_TRY(hipStreamCreateWithFlags(&lds_stream, hipStreamNonBlocking));
                 HIP_TRY(hipEventCreateWithFlags(&fork, hipEventDisableTiming));
@@ -685,8 +762,7 @@ struct SurfaceGroup {
                 HIP_TRY(hipEventRecord(fork, stream));
                 HIP_TRY(hipStreamWaitEvent(lds_stream, fork, 0));
             }
-            lds_launcher(D, sched)(dim3((unsigned)lds_idx.size()), lds_bytes, lds_is_wide, beside ? lds_stream : stream,
-                                   d_desc, d_lds_idx);
+            lds_launcher(D, sched)(dim3((unsigned)lds_idx.size()), lds, beside ? lds_stream : stream, d_desc, d_lds_idx);
             HIP_TRY(hipGetLastError());
             if (beside) HIP_TRY(hipEventRecord(join, lds_stream));
         }
@@ -1180,7 +1256,7 @@ rsos_status rsos_kernel_name(rsos_surface *s, char *buf, int32_t len)
         snprintf(buf, (size_t)len, "block_sweep<%d,%d,%d,%d,%s,%d>", v->D, v->TX, v->TY, v->NT,
                  v->elem == 1 ? "int8,int16" : v->elem == 2 ? "int16,void" : "int32,void", g.sched);
     else
-        snprintf(buf, (size_t)len, g.lds_is_wide ? "lds_run32<%d,256,%d>" : "lds_run<%d,512,%d>", g.D, g.sched);
+        snprintf(buf, (size_t)len, g.lds.mode == LdsMode::kLane ? "lds_run32<%d,256,%d>" : "lds_run<%d,512,%d>", g.D, g.sched);
     return RSOS_OK;
 }
 
@@ -1483,10 +1559,7 @@ extern "C" rsos_status rsos_sweep_static(const rsos_params *p, int32_t *d_h, int
     HIP_TRY(hipGetLastError());
     if (!v) {
         // the whole surface in one workgroup's LDS, all sweeps in one launch
-        bool wide;
-        size_t shm;
-        lds_plan(D, sched, {{p->L, p->N}}, &wide, &shm);
-        lds_launcher(D, sched)(dim3(1), shm, wide, s, dd, (const int *)(base + kScratchIdx));
+        lds_launcher(D, sched)(dim3(1), lds_plan(D, sched, {{p->L, p->N}}), s, dd, (const int *)(base + kScratchIdx));
         HIP_TRY(hipGetLastError());
     } else {
         BlockLaunch k = sched == 1 ? v->launch_dt : v->launch;

@@ -1877,18 +1877,18 @@ struct LdsRun {
     {
         return L <= 64 && L / D * (L / D) / phases * kLdsWin <= kLdsThreads / 2;
     }
-    __host__ __device__ static int list_bytes(int L, int phases)  // of one set
+    __host__ __device__ static int list_bytes(int L, int phases, bool ahead)  // of one set
     {
-        return L * L / (ahead(L, phases) ? 1 : phases) * kLdsWin * 2 + 16;  // one pair is read beyond the last
+        return L * L / (ahead ? 1 : phases) * kLdsWin * 2 + 16;  // one pair is read beyond the last
     }
-    __host__ __device__ static int bytes(int L, int phases)
+    __host__ __device__ static int bytes(int L, int phases, bool ahead)
     {
-        return lattice_bytes(L) + list_bytes(L, phases) * (ahead(L, phases) ? 2 : 1);
+        return lattice_bytes(L) + list_bytes(L, phases, ahead) * (ahead ? 2 : 1);
     }
 };
 
 template <int D, int NT, int SCHED = 0>
-__global__ __launch_bounds__(NT) void lds_run(SurfDev *__restrict__ descs, const int *__restrict__ which)
+__global__ __launch_bounds__(NT) void lds_run(SurfDev *__restrict__ descs, const int *__restrict__ which, int may_ahead)
 {
     using R = LdsRun<D>;
     using TB = TileBits<D>;
@@ -1907,14 +1907,14 @@ __global__ __launch_bounds__(NT) void lds_run(SurfDev *__restrict__ descs, const
     if (t >= t_end) return;
     const int L = d.L, N = d.N, T = d.T, tid = threadIdx.x;
     const uint32_t k0 = d.key0, k1 = d.key1;
-    const bool ahead = R::ahead(L, PH);
+    const bool ahead = may_ahead && R::ahead(L, PH);
     const int ntiles = T * T / PH, ngroups = (ntiles + 15) / 16;
     const int all = ahead ? T * T : ntiles;   // tiles of a set of lists
     // threads that lay out steps while the others make attempts
     const int makers = min(NT, (ntiles * kLdsWin + 63) & ~63);
     int16_t *h = (int16_t *)lds_dyn + P + 1;  // site (0, 0); the frame's at index -1
     uint16_t *const lists = (uint16_t *)(lds_dyn + R::lattice_bytes(L));
-    const int set = R::list_bytes(L, PH) / 2;  // entries of a set
+    const int set = R::list_bytes(L, PH, ahead) / 2;  // entries of a set
     // a site that no attempt changes, for lanes without one: N above all its
     // neighbours
     int16_t *const idle = h + (L + 2 * D + 2) * P;  // row L + 2 D + 3 of the array

@@ -99,3 +99,27 @@ def test_sums_are_the_lattice_s_own(rsos, oracle, L, N, D, schedule):
         torch.cuda.synchronize()
         assert np.array_equal(log.cpu().numpy().reshape(n, 3), r_log[:, 1:4]), f"sums given as {sums}"
         assert np.array_equal(bufs[n & 1].cpu().numpy(), r_h)
+
+
+@pytest.mark.parametrize("sizes,each,D,schedule", [
+    ((64,), 257, 8, "checkerboard"),      # one phase's steps at a time
+    ((64,), 2048, 8, "checkerboard"),
+    ((112,), 768, 8, "checkerboard"),
+    ((32, 64), 1024, 8, "checkerboard"),
+    ((64,), 300, 8, "double"),
+    ((64,), 300, 16, "checkerboard"),
+    ((32,), 700, 4, "checkerboard"),
+])
+def test_many_surfaces(rsos, oracle, sizes, each, D, schedule):
+    """More surfaces than are resident at once: the kernel and the step lists
+    go by their number, and the results do not."""
+    print(f"[lds] {each} of each of {sizes} D={D} {schedule}", flush=True)
+    specs = [(L, 1 + k % 2, 11 * L + k) for L in sizes for k in range(each)]
+    b = rsos.Batch(specs, D=D, schedule=schedule, log_cap=8)
+    b.sweep(3)
+    b.sweep(2)
+    for i in (0, 1, len(specs) // 2, len(specs) - 1):
+        L, N, seed = specs[i]
+        r_h, r_log = _oracle(oracle, workloads.flat(L), L, N, D, seed, 5, schedule)
+        _same(b.log(i, 1, 5), r_log, b.heights(i), r_h, f"surface {i} of {len(specs)}")
+    b.close()
