@@ -146,9 +146,9 @@ def bench_single(L, N, D, seed, steps, warmup, packed=False, schedule="checkerbo
     torch.cuda.synchronize()
     s.sweep(min(steps, 400))
     launches, mean_ms, _ = s.timing_read()
+    kname = s.kernel_name()  # of the launches timed
     s.timing(False)
     w = s.width()
-    kname = s.kernel_name()
     # height-distribution moments of the final state (one read of the
     # lattice per call, synchronous)
     s.moments()

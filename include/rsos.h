@@ -169,10 +169,12 @@ rsos_status rsos_init(rsos_surface **out, const rsos_params *p, int32_t *d_h, in
  * on the surface's stream; t += n_mcs.  n_mcs = 0 does nothing; n_mcs < 0
  * or t + n_mcs > 2^32 gives RSOS_E_INVAL.  Checks the overflow bound
  * H = max(h0) + min(t + N L, D^2 t) < 2^31 and L^2 H^2 < 2^63 before
- * enqueuing anything (RSOS_E_OVERFLOW: no device work, t unchanged).  Each
- * sweep is one kernel launch (runs of them replayed as hipGraphs when the
- * surface has a stream; the graph is captured by rsos_init, never inside
- * rsos_sweep); the exact sums of the sweep are part of it. */
+ * enqueuing anything (RSOS_E_OVERFLOW: no device work, t unchanged).  A
+ * sweep is one kernel launch, its exact sums included; where a launch's
+ * latency is the bound (see rsos_kernel_name) two sweeps share one, in calls
+ * of four sweeps and more, and a surface in LDS makes all sweeps of a call in
+ * one.  Runs of launches are replayed as hipGraphs when the surface has a
+ * stream; the graph is captured by rsos_init, never inside rsos_sweep. */
 rsos_status rsos_sweep(rsos_surface *s, int64_t n_mcs);
 
 /* Synchronises the stream and returns the record of the current time t:
@@ -200,9 +202,10 @@ rsos_status rsos_time(rsos_surface *s, int64_t *t, int32_t **d_current);
 /* Kernel timing.  While enabled, every sweep's tile-block kernels are
  * launched with HIP events on the surface's stream that the runtime records
  * when the first kernel starts and the last one ends (hipExtLaunchKernel;
- * sweeps are then issued one by one, not as hipGraph replays).  rsos_timing_read
- * synchronises and returns the number of timed launches and their mean and
- * total duration in milliseconds; it also clears the record. */
+ * sweeps are then issued one by one, one per launch and not as hipGraph
+ * replays, also for a surface whose other calls make two per launch).
+ * rsos_timing_read synchronises and returns the number of timed launches and
+ * their mean and total duration in milliseconds; it also clears the record. */
 rsos_status rsos_timing(rsos_surface *s, int enable);
 rsos_status rsos_timing_read(rsos_surface *s, int64_t *launches, double *mean_ms, double *total_ms);
 
@@ -210,10 +213,15 @@ rsos_status rsos_timing_read(rsos_surface *s, int64_t *launches, double *mean_ms
  * form rocprofv3 shows its template arguments: e.g.
  * "block_sweep<8,32,8,256,int8,int16,0>" (D, tiles per block in x and y,
  * threads, LDS element type, the wider type of blocks that do not fit it,
- * schedule), "block_sweep16<8,32,8,256,0>" with 16-bit storage, or
- * "lds_run<8,512,0>" for an LDS-resident surface; written NUL-terminated
- * into buf (at most len bytes).  With several kernel instances (a tuned
- * batch) the first one. */
+ * schedule: 0 checkerboard, 1 double tiling, 2 checkerboard with attempts in
+ * steps), "block_sweep16<8,32,8,256,0>" with 16-bit storage,
+ * "block_sweep2<8,32,8,256,false>" (D, tiles, threads, attempts in steps)
+ * where two sweeps share a launch, or "lds_run<8,512,0>" for an LDS-resident
+ * surface; written NUL-terminated into buf (at most len bytes).  With several
+ * kernel instances (a tuned batch) the first one.  A surface that makes two
+ * sweeps per launch makes the last one to three sweeps of a call by a
+ * block_sweep, and all sweeps while rsos_timing is enabled; that instance is
+ * named while it is. */
 rsos_status rsos_kernel_name(rsos_surface *s, char *buf, int32_t len);
 
 /* Frees the handle and library-owned memory (never d_h, never a

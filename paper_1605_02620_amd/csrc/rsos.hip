@@ -1250,11 +1250,14 @@ rsos_status rsos_kernel_name(rsos_surface *s, char *buf, int32_t len)
     if (!buf || len < 1) return fail(RSOS_E_INVAL, "bad buffer");
     const SurfaceGroup &g = s->g;
     const Variant *v = g.shapes.empty() ? nullptr : g.shapes[0].variant;
-    if (v && g.packed)
+    const Pair *q = v && !g.timing ? g.shapes[0].pair : nullptr;  // (timed launches are of single sweeps)
+    if (q)
+        snprintf(buf, (size_t)len, "block_sweep2<%d,%d,%d,%d,%s>", q->D, q->TX, q->TY, q->NT, q->steps ? "true" : "false");
+    else if (v && g.packed)
         snprintf(buf, (size_t)len, "block_sweep16<%d,%d,%d,%d,0>", v->D, v->TX, v->TY, v->NT);
     else if (v)
         snprintf(buf, (size_t)len, "block_sweep<%d,%d,%d,%d,%s,%d>", v->D, v->TX, v->TY, v->NT,
-                 v->elem == 1 ? "int8,int16" : v->elem == 2 ? "int16,void" : "int32,void", g.sched);
+                 v->elem == 1 ? "int8,int16" : v->elem == 2 ? "int16,void" : "int32,void", v->steps ? 2 : g.sched);
     else
         snprintf(buf, (size_t)len, g.lds.mode == LdsMode::kLane ? "lds_run32<%d,256,%d>" : "lds_run<%d,512,%d>", g.D, g.sched);
     return RSOS_OK;
