@@ -177,7 +177,8 @@ def bench_single(L, N, D, seed, steps, warmup, packed=False, schedule="checkerbo
 
 
 def _tune_summary(t):
-    return {"shape": f"{t['TX']}x{t['TY']} tiles, {t['NT']} threads, {t['elem']}-byte staging",
+    pair = ", two sweeps per launch" if t["elem"] & 64 else ""
+    return {"shape": f"{t['TX']}x{t['TY']} tiles, {t['NT']} threads, {t['elem'] & 63}-byte staging{pair}",
             "xcd_order": {0: "in order", 1: "runs of 16 per XCD", 2: "column strips per XCD"}[t["xmode"]],
             "graph_sweeps": t["graph_sweeps"], "candidates": t["candidates"],
             "ms_per_sweep_tuned": round(t["ms_per_sweep"], 4),

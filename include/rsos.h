@@ -404,8 +404,10 @@ rsos_status rsos_engine_stats(rsos_engine *e, int64_t out[6]);
  * chunk sweeps the running jobs with the autotuner's batched choice for the
  * (L, N) class that holds the most sites among them, when that variant fits
  * every running job (a class is tuned on first use, between chunks; load a
- * saved cache with rsos_tune_load to avoid that); otherwise, and with
- * enable = 0 (the default), with the first variant that fits them all.
+ * saved cache with rsos_tune_load to avoid that; few jobs make two sweeps per
+ * launch all the same, unless the choice was entered by rsos_tune_set);
+ * otherwise, and with enable = 0 (the default), with two sweeps per launch or
+ * the first variant that fits them all.
  * Results never change. */
 rsos_status rsos_engine_tune(rsos_engine *e, int32_t enable);
 
@@ -417,9 +419,10 @@ rsos_status rsos_engine_destroy(rsos_engine *e);
 /* is part of the result and is never tuned; the autotuner picks, per key  */
 /* (device, D, L, N, storage and schedule flags, alone or batched), the    */
 /* launch knobs that leave every result unchanged: the tile-block variant  */
-/* (block shape, threads per workgroup, LDS staging type), the order in    */
-/* which workgroups take blocks across the 8 XCDs, and the sweeps per      */
-/* captured hipGraph.  It times every candidate with HIP events on a       */
+/* (block shape, threads per workgroup, LDS staging type; one sweep per    */
+/* launch or two), the order in which workgroups take blocks across the 8  */
+/* XCDs, and the sweeps per captured hipGraph.  What is chosen or entered  */
+/* is what runs.  It times every candidate with HIP events on a       */
 /* scratch workload of the key (flat surfaces; one surface when alone,     */
 /* ceil(2^24 / L^2) surfaces in one launch when batched; L > 16384 tuned   */
 /* on a 16384^2 stand-in) and caches the fastest for the process.  Tuning */
@@ -431,7 +434,10 @@ rsos_status rsos_engine_destroy(rsos_engine *e);
 /* One launch configuration.
  *   TX, TY, NT    tiles per block in x and y, threads per workgroup;
  *   elem          LDS bytes per staged site (1: int8, with int16
- *                 sub-blocks where a block's range does not fit; 2; 4);
+ *                 sub-blocks where a block's range does not fit; 2; 4),
+ *                 or-ed with RSOS_TUNE_PAIR for launches of two sweeps
+ *                 (the sweeps of a call beyond whole fours are then made by
+ *                 the first variant that fits; 2: attempts in steps);
  *   xmode         workgroup -> block order: 0 in order, 1 runs of 16
  *                 blocks per XCD, 2 one column strip of blocks per XCD
  *                 (single surfaces whose block columns divide by 8);
@@ -441,8 +447,9 @@ rsos_status rsos_engine_destroy(rsos_engine *e);
  *                 entered by rsos_tune_set (or loaded as such);
  *   ms_per_sweep  the chosen configuration's mean sweep time on the
  *                 tuning workload (0 if not measured);
- *   ms_first_fit  the untuned default's (first fitting variant, xmode 1)
- *                 on the same workload. */
+ *   ms_first_fit  the untuned default's (two sweeps per launch or the first
+ *                 fitting variant, xmode 1) on the same workload. */
+#define RSOS_TUNE_PAIR 64
 typedef struct {
     int32_t TX, TY, NT, elem;
     int32_t xmode;
@@ -466,7 +473,8 @@ rsos_status rsos_tune_candidates(const rsos_params *p, int32_t batch, rsos_tune_
 
 /* Enters a configuration for p's key without timing (it must fit the key:
  * RSOS_E_INVAL otherwise); later handles created with RSOS_FLAG_TUNE use
- * it.  Meant for tests and for reusing results of another process. */
+ * it (a batch of classes with different choices, see rsos_batch_init, may
+ * time them together).  Meant for tests and for reusing results of another process. */
 rsos_status rsos_tune_set(const rsos_params *p, int32_t batch, const rsos_tune_t *choice);
 
 /* Empties the cache. */

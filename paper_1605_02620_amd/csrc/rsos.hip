@@ -537,12 +537,19 @@ struct Shape {
     int *d_owner2 = nullptr; // as d_owner
 };
 
-// A launch choice for one surface: kernel variant, block order and sweeps
-// per captured graph (none of them changes results).
+// A launch choice for one surface: the kernel variant, or the blocks of two
+// sweeps per launch (with the first variant that fits for single sweeps), the
+// block order and the sweeps per captured graph (none of them changes
+// results).
 struct Choice {
     const Variant *v = nullptr;
+    const Pair *pair = nullptr;
     int xmode = 1;
     int graph_k = 0;
+    bool entered = false;  // by rsos_tune_set, not timed
+
+    bool made() const { return v || pair; }
+    bool same_kernel(const Choice &o) const { return v == o.v && pair == o.pair && xmode == o.xmode; }
 };
 
 // ---------------------------------------------------------------------------
@@ -577,8 +584,7 @@ struct SurfaceGroup {
     hipStream_t lds_stream = nullptr;
     hipEvent_t fork = nullptr, join = nullptr;
     Staging staging;
-    bool pairs = true;                 // two sweeps may share a launch
-    bool any_pair = false;             // and do, in some shape
+    bool any_pair = false;             // two sweeps share a launch, in some shape
     hipGraphExec_t graph = nullptr;    // graph_k sweeps that every block-path surface makes
     hipGraphExec_t graph1 = nullptr;   // as many, one per launch, each bounded by t_end (where it differs)
     bool timing = false;                             // bracket block launches with events
@@ -611,19 +617,26 @@ struct SurfaceGroup {
         if (packed && !lds_idx.empty()) return fail(RSOS_E_INVAL, "16-bit storage needs the tile-block path");
         if (const char *xm = getenv("RSOS_XMODE")) xmode = atoi(xm) == 0 ? 0 : atoi(xm) == 2 ? 2 : 1;
         bool tuned = !blk_idx.empty() && want.size() == host.size();
-        for (int i : blk_idx) tuned = tuned && want[i].v != nullptr;
+        for (int i : blk_idx) tuned = tuned && want[i].made();
         std::vector<std::vector<int>> members;
         if (tuned) {
             for (int i : blk_idx) {
                 size_t g = 0;
-                while (g < shapes.size() && !(shapes[g].variant == want[i].v && shapes[g].xmode == want[i].xmode)) ++g;
+                while (g < shapes.size() && !want[members[g][0]].same_kernel(want[i])) ++g;
                 if (g == shapes.size()) {
                     shapes.push_back(Shape());
                     shapes.back().variant = want[i].v;
+                    shapes.back().pair = want[i].pair;
                     shapes.back().xmode = want[i].xmode;
                     members.emplace_back();
                 }
                 members[g].push_back(i);
+            }
+            for (size_t g = 0; g < shapes.size(); ++g) {
+                if (shapes[g].variant) continue;
+                std::vector<std::pair<int, int>> ln;
+                for (int i : members[g]) ln.push_back({host[i].L, host[i].N});
+                if (!(shapes[g].variant = pick_variant(D, ln))) return fail(RSOS_E_INVAL, "no tile-block shape fits these lattice sizes");
             }
             graph_k = 0;
             for (int i : blk_idx) graph_k = std::max(graph_k, want[i].graph_k);
@@ -633,6 +646,7 @@ struct SurfaceGroup {
             if (!v) return fail(RSOS_E_INVAL, "no tile-block shape fits these lattice sizes");
             shapes.push_back(Shape());
             shapes.back().variant = v;
+            if (!packed && sched == 0) shapes.back().pair = pick_pair(D, LN);
             shapes.back().xmode = xmode;
             members.push_back(blk_idx);
         }
@@ -645,12 +659,7 @@ struct SurfaceGroup {
             sh.count = (int)members[g].size();
             long long blocks = 0;
             long long blocks2 = 0;
-            if (pairs && !packed && sched == 0) {
-                std::vector<std::pair<int, int>> ln;
-                for (int i : members[g]) ln.push_back({host[i].L, host[i].N});
-                sh.pair = pick_pair(D, ln);
-                any_pair = any_pair || sh.pair;
-            }
+            any_pair = any_pair || sh.pair;
             for (int i : members[g]) {
                 SurfDev &sd = host[i];
                 const int T = sd.L / D;
