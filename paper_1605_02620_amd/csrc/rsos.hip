@@ -851,12 +851,15 @@ struct SurfaceGroup {
         return RSOS_OK;
     }
 
-    // Captures the graph of graph_k sweeps when the group is created, so
-    // that no rsos_sweep call pays for a capture (surfaces on a stream).
+    // Captures the graphs of graph_k sweeps when the group is created, so
+    // that no sweep call pays for a capture (surfaces on a stream): the second
+    // one for the sweeps that only some of several surfaces make.
     rsos_status prepare_graph()
     {
         if (stream == nullptr || blk_idx.empty() || graph) return RSOS_OK;
-        return capture_graph(graph_k, &graph, any_pair);
+        rsos_status st = capture_graph(graph_k, &graph, any_pair);
+        if (st == RSOS_OK && any_pair && blk_idx.size() > 1) st = capture_graph(graph_k, &graph1, false);
+        return st;
     }
 
     rsos_status capture_graph(int k, hipGraphExec_t *gr, bool four)

@@ -72,3 +72,32 @@ def test_pairs_batch(rsos, oracle, L, copies):
         _check(oracle, b.log(k, 1, n), b.heights(k), workloads.flat(L), L, specs[k][1], specs[k][2], 0, n, f"surface {k}")
     assert [int(x["t"]) for x in w] == [int(x) for x in total]
     b.close()
+
+
+def test_uneven_call_captures_nothing(rsos):
+    """The first call with unequal counts makes as many runtime calls as a
+    later one: its graph was captured when the batch was created."""
+    import torch
+    from paper_1605_02620_amd._lib import RsosError, lib
+    stream = torch.cuda.Stream()
+
+    def calls(before):
+        """Runtime calls of an uneven call after `before` others."""
+        for n in range(1, 64):
+            b = rsos.Batch([(256, 1, 1), (256, 1, 2)], stream=stream)
+            for _ in range(before):
+                b.sweep([0, 70])
+                b.width()
+            lib().rsos_debug_fail(n)
+            try:
+                b.sweep([0, 70])
+            except RsosError:
+                continue
+            finally:
+                lib().rsos_debug_fail(0)
+                b.close()
+            return n - 1
+        raise AssertionError("no call went through")
+
+    print("[pairs] runtime calls of uneven calls", flush=True)
+    assert calls(0) <= calls(1) + 3  # a rewrite of the descriptors is three
