@@ -569,7 +569,7 @@ struct SurfaceGroup {
     long long *d_acc = nullptr;        // kAccWords per block-path surface
     std::vector<int32_t *> readout;    // 16-bit storage: int32[L^2] device scratch per surface
     long long *d_ps = nullptr;         // power sums: per-workgroup partials, then the result
-    long long *d_rec = nullptr;        // the surfaces' current records (read_widths)
+    long long *d_rec = nullptr;        // the surfaces' current records (read_widths; batches)
     int xmode = 1;                     // workgroup -> block order (rsosk::block_map) without a choice
     std::vector<Shape> shapes;         // block-path surfaces by kernel instance
     std::vector<Choice> want;          // per surface: a tuned launch choice (or none); read by setup()
@@ -905,7 +905,6 @@ struct SurfaceGroup {
     {
         const int n = (int)host.size();
         rsos_status st;
-        if (!d_rec && (st = dev_alloc((void **)&d_rec, sizeof(long long) * 3 * n)) != RSOS_OK) return st;
         hipLaunchKernelGGL(rsosk::gather_records, dim3((unsigned)(n + 255) / 256), dim3(256), 0, stream, d_desc, n, d_rec);
         HIP_TRY(hipGetLastError());
         if ((st = staging.copy_from(d_rec, sizeof(long long) * 3 * n, stream)) != RSOS_OK) return st;
@@ -1371,6 +1370,7 @@ rsos_status rsos_batch_init(rsos_batch **out, int32_t n, const rsos_params *p, i
             if (!uses_lds(p[i].L)) g.want[i] = plan[k++];
     }
     if ((st = mark(g, g.setup())) != RSOS_OK) { g.destroy(); delete b; return st; }
+    if ((st = g.dev_alloc((void **)&g.d_rec, sizeof(long long) * 3 * n)) != RSOS_OK) { g.destroy(); delete b; return st; }
     for (int i = 0; i < n; ++i)
         if ((st = g.load_initial(i, nullptr, 0)) != RSOS_OK || (st = g.init_record(i, 0, 0)) != RSOS_OK) {
             g.destroy();
