@@ -131,3 +131,32 @@ def test_packed_readout_alignment(rsos, L, N, amp, shift):
     d = h0.astype(np.int64) - int(h0.astype(np.int64).sum()) // (L * L)
     assert [m["c1"], m["c2"], m["c3"], m["c4"]] == [int((d ** k).sum()) for k in (1, 2, 3, 4)]
     s.close()
+
+
+@pytest.mark.parametrize("values", ["small", "edge", "wide"])
+@pytest.mark.parametrize("L,N,packed", [(144, 2 ** 31 - 1, False), (272, 2 ** 31 - 1, False), (1040, 2 ** 31 - 1, False),
+                                        (192, 12, True), (1216, 12, True)])
+def test_partial_groups(rsos, L, N, packed, values):
+    """Site counts that the workgroups' groups of 8192 do not divide, and
+    heights on both sides of each bound of the sums (128 and 2^11 from the
+    reference)."""
+    n, rng = L * L, np.random.default_rng(L)
+    if packed:  # within the restriction: hills of the given height
+        top = {"small": 60, "edge": 256, "wide": N * L // 4}[values]
+        h0 = workloads.cone(L, N, height=top, seed=L) + 70000
+    else:
+        off = {"small": rng.integers(-100, 101, n), "edge": rng.choice([-129, -128, -127, 0, 126, 127, 128, 129], n),
+               "wide": rng.choice([-5000, -2049, -2048, -2047, -128, 3, 127, 2047, 2048, 2049, 5000], n)}[values]
+        h0 = 70000 + off
+    h0 = np.ascontiguousarray(h0.reshape(-1).astype(np.int32))
+    print(f"[moments] L={L} packed={packed} {values}", flush=True)
+    # (16-bit storage: the sides that D = 8 takes are multiples of 128)
+    s = rsos.Surface(L, N=N, seed=5, D=4 if packed else 8, h0=h0, packed=packed)
+    m = s.moments()
+    h = h0.astype(np.int64)
+    ref = int(h.sum()) // n
+    d = [int(x) for x in np.unique(h - ref)]
+    counts = np.unique(h - ref, return_counts=True)[1]
+    assert m["ref"] == ref
+    assert [m["c1"], m["c2"], m["c3"], m["c4"]] == [sum(int(c) * x ** k for x, c in zip(d, counts)) for k in (1, 2, 3, 4)]
+    s.close()
