@@ -923,7 +923,8 @@ struct SurfaceGroup {
         if (packed) {
             // residues -> int32 on the device (needs floor(S1 / L^2) of time t)
             int32_t *out = dst_is_device ? dst : readout[i];
-            hipLaunchKernelGGL(rsosk::unpack16, dim3(grid_for(n)), dim3(256), 0, stream,
+            hipLaunchKernelGGL((long long)n > rsosk::kStreamSites ? rsosk::unpack16<true> : rsosk::unpack16<false>,
+                               dim3(grid_for(n)), dim3(256), 0, stream,
                                (const uint16_t *)s.buf[s.t & 1], out, (long long)n,
                                (const long long *)(s.acc + rsosk::kMeanWord));
             HIP_TRY(hipGetLastError());

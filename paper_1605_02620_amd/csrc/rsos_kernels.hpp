@@ -1786,8 +1786,10 @@ __global__ void gather_records(const SurfDev *__restrict__ descs, int n, long lo
 // Conversions between int32 heights and 16-bit residues, eight sites (one
 // 16-byte chunk of residues) per thread and turn; n % 8 == 0, residues
 // 16-byte aligned.  The int32 side is the caller's and need not be: then its
-// words move one by one.  Both are bound by HBM: one residue at a time,
-// unpack16 took 472 us at L = 16384 (1.5 GiB), so 393.
+// words move one by one.  Both are bound by memory.  A readout that the 256 MiB
+// cache in front of HBM cannot hold (6 bytes a site) streams past it: with one
+// residue at a time L = 16384 took 493 us, so 413, L = 8192 140 and 103; what
+// fits goes through it (L = 6144: 48 us, streamed 62).
 __global__ void pack16(const int32_t *__restrict__ src, uint16_t *__restrict__ dst, long long n)
 {
     for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n / 8; i += (long long)gridDim.x * blockDim.x) {
@@ -1808,13 +1810,17 @@ __global__ void pack16(const int32_t *__restrict__ src, uint16_t *__restrict__ d
     }
 }
 
+constexpr long long kStreamSites = (256ll << 20) / 6;  // more sites than these stream
+template <bool STREAM>
 __global__ void unpack16(const uint16_t *__restrict__ src, int32_t *__restrict__ dst, long long n,
                          const long long *__restrict__ mean_floor)
 {
     const int m0 = (int)*mean_floor;  // heights fit int32
     const uint32_t r0 = ((uint32_t)m0 & 0xFFFFu) * 0x10001u;
     for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n / 8; i += (long long)gridDim.x * blockDim.x) {
-        const v4u v = __builtin_nontemporal_load((const gv4u *)src + i);
+        v4u v;
+        if constexpr (STREAM) v = __builtin_nontemporal_load((const gv4u *)src + i);
+        else v = ((const gv4u *)src)[i];
         v4u o[2];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
@@ -1823,8 +1829,13 @@ __global__ void unpack16(const uint16_t *__restrict__ src, int32_t *__restrict__
             o[k / 2][2 * (k % 2) + 1] = (uint32_t)(m0 + ((int)d >> 16));
         }
         if (((uintptr_t)dst & 15) == 0) {
-            __builtin_nontemporal_store(o[0], (gv4u *)dst + 2 * i);
-            __builtin_nontemporal_store(o[1], (gv4u *)dst + 2 * i + 1);
+            if constexpr (STREAM) {
+                __builtin_nontemporal_store(o[0], (gv4u *)dst + 2 * i);
+                __builtin_nontemporal_store(o[1], (gv4u *)dst + 2 * i + 1);
+            } else {
+                ((gv4u *)dst)[2 * i] = o[0];
+                ((gv4u *)dst)[2 * i + 1] = o[1];
+            }
         } else {
             for (int k = 0; k < 8; ++k) as_global(dst)[8 * i + k] = (int32_t)o[k / 4][k % 4];
         }

@@ -164,3 +164,25 @@ def test_packed_full_size_invariants(rsos):
     assert int(lg["s1"][-1]) == int(lg["accepted"].sum()) == int(h.sum())
     assert int(lg["s2"][-1]) == int((h * h).sum())
     assert np.all(np.diff(lg["s1"]) == lg["accepted"][1:])
+
+
+@pytest.mark.parametrize("shift", [0, 1])
+@pytest.mark.parametrize("L", [6656, 6784])  # either side of what the cache holds
+def test_readout_of_large_lattices(rsos, L, shift):
+    """16-bit storage gives the int32 surface's heights through the cache and
+    past it, into buffers that are 16-byte aligned or not."""
+    import ctypes
+
+    import torch
+    from paper_1605_02620_amd import _lib
+    print(f"[packed] readout L={L} shift={shift}", flush=True)
+    s, p = rsos.Surface(L, N=1, seed=3), rsos.Surface(L, N=1, seed=3, packed=True)
+    s.sweep(2)
+    p.sweep(2)
+    out = torch.full((L * L + 4,), -7, dtype=torch.int32, device="cuda")
+    _lib.check(_lib.lib().rsos_heights(p._h, ctypes.c_void_p(out.data_ptr() + 4 * shift), 1))
+    s.width()
+    assert torch.equal(out[shift:shift + L * L], s.heights_tensor())
+    assert int((out[:shift] != -7).sum()) == 0 and int((out[shift + L * L:] != -7).sum()) == 0
+    s.close()
+    p.close()
