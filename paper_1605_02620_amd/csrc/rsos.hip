@@ -285,14 +285,8 @@ const Pair *pick_pair(int D, const std::vector<std::pair<int, int>> &LN)
     return nullptr;
 }
 
-// A surface's blocks of shape q, the first of them number start.
-int place_pair(SurfDev &d, const Pair &q, long long start)
-{
-    d.nbx2 = blocks_along(d.T, q.TX);
-    d.nblocks2 = d.nbx2 * blocks_along(d.T, q.TY);
-    d.block_start2 = (int)start;
-    return d.nblocks2;
-}
+// The blocks of shape q of a surface.
+int pair_blocks(const Pair &q, int T) { return blocks_along(T, q.TX) * blocks_along(T, q.TY); }
 
 bool uses_lds(int L);
 
@@ -667,13 +661,14 @@ struct SurfaceGroup {
                 sd.nblocks = sd.nbx * blocks_along(T, sh.variant->TY);
                 sd.block_start = (int)blocks;
                 blocks += sd.nblocks;
-                if (sh.pair) blocks2 += place_pair(sd, *sh.pair, blocks2);
+                sd.block_start2 = (int)blocks2;
+                if (sh.pair) blocks2 += pair_blocks(*sh.pair, T);
                 if (blocks > (1ll << 30)) return fail(RSOS_E_INVAL, "too many tile blocks");
                 rows.push_back(i);
             }
             sh.total_blocks = (int)blocks;
             sh.pair_blocks = (int)blocks2;
-            sh.pair_xmode = sh.xmode == 2 && sh.pair && !(sh.count == 1 && host[members[g][0]].nbx2 % 8 == 0) ? 1 : sh.xmode;
+            sh.pair_xmode = sh.xmode == 2 && sh.pair && !(sh.count == 1 && blocks_along(host[members[g][0]].T, sh.pair->TX) % 8 == 0) ? 1 : sh.xmode;
             if (sh.xmode == 2 && !(sh.count == 1 && host[members[g][0]].nbx % 8 == 0)) sh.xmode = 1;
         }
         const int nblk_rows = (int)rows.size();
@@ -699,7 +694,8 @@ struct SurfaceGroup {
             for (int k = 0; k < sh.count; ++k) {
                 const SurfDev &sd = host[rows[sh.first + k]];
                 for (int b = 0; b < sd.nblocks; ++b) own[(size_t)sd.block_start + b] = k;
-                for (int b = 0; b < sd.nblocks2; ++b) own[(size_t)sh.total_blocks + sd.block_start2 + b] = k;
+                for (int b = 0; sh.pair && b < pair_blocks(*sh.pair, sd.T); ++b)
+                    own[(size_t)sh.total_blocks + sd.block_start2 + b] = k;
             }
             if ((st = dev_alloc((void **)&sh.d_owner, sizeof(int) * own.size())) != RSOS_OK) return st;
             HIP_TRY(hipMemcpy(sh.d_owner, own.data(), sizeof(int) * own.size(), hipMemcpyHostToDevice));
@@ -730,7 +726,8 @@ struct SurfaceGroup {
         SurfDev *h = (SurfDev *)staging.host;
         for (int k = 0; k < n; ++k) {
             h[k] = host[rows[k]];
-            h[k].slot = h[k].t % h[k].log_cap;
+            // (most surfaces of a batch are at one time: no division for these)
+            h[k].slot = k && h[k].t == h[k - 1].t && h[k].log_cap == h[k - 1].log_cap ? h[k - 1].slot : h[k].t % h[k].log_cap;
         }
         return staging.copy_to(d_desc, sizeof(SurfDev) * n, stream);
     }
@@ -812,7 +809,7 @@ struct SurfaceGroup {
     void launch_four()
     {
         for (const Shape &sh : shapes) {
-            const int nbx2 = sh.count == 1 ? host[rows[sh.first]].nbx2 : 0;
+            const int nbx2 = sh.count == 1 && sh.pair ? blocks_along(host[rows[sh.first]].T, sh.pair->TX) : 0;
             for (int i = 0; i < 4; ++i)
                 if (!sh.pair) launch_shape(sh);
                 else if (i % 2 == 0)
@@ -1553,6 +1550,7 @@ extern "C" rsos_status rsos_sweep_static(const rsos_params *p, int32_t *d_h, int
     d.t = t0;
     d.slot = t0 % kStaticLogCap;
     d.t_end = t0 + n_mcs;
+    d.mode = rsosk::kOwnSums;
     d.key0 = (uint32_t)(p->seed & 0xFFFFFFFFu);
     d.key1 = (uint32_t)(p->seed >> 32);
     d.L = p->L;
@@ -1567,7 +1565,6 @@ extern "C" rsos_status rsos_sweep_static(const rsos_params *p, int32_t *d_h, int
         d.nblocks = d.nbx * blocks_along(d.T, v->TY);
         d.block_start = 0;
         if (sched == 0) pair = pick_pair(D, {{p->L, p->N}});
-        if (pair) place_pair(d, *pair, 0);
     }
     hipStream_t s = (hipStream_t)stream;
     SurfDev *dd = (SurfDev *)(base + kScratchDesc);
@@ -1581,7 +1578,8 @@ extern "C" rsos_status rsos_sweep_static(const rsos_params *p, int32_t *d_h, int
         BlockLaunch k = sched == 1 ? v->launch_dt : v->launch;
         long long left = n_mcs;
         for (; pair && left >= 4; left -= 4)
-            for (int i = 0; i < 2; ++i) pair->launch(dim3(d.nblocks2), s, dd, 1, nullptr, 1, d.nbx2);
+            for (int i = 0; i < 2; ++i)
+                pair->launch(dim3(pair_blocks(*pair, d.T)), s, dd, 1, nullptr, 1, blocks_along(d.T, pair->TX));
         for (; left > 0; --left) k(dim3(d.nblocks), s, dd, 1, nullptr, 1, d.nbx, nullptr, nullptr);
         HIP_TRY(hipGetLastError());
     }

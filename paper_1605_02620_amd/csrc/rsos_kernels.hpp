@@ -116,21 +116,25 @@ __device__ __forceinline__ void store4(gint32 *p, const int4 v)
 }
 
 struct SurfDev {
-    int32_t *buf[2];      // state after t sweeps is in buf[t & 1] (see flip)
+    int32_t *buf[2];      // state after t sweeps is in buf[t & 1] (see mode)
     long long *log;       // 3 * log_cap int64: (S1, S2, A) of time tau at slot tau % log_cap
     long long *acc;       // kAccWords int64: accumulators (zero between sweeps), mean floor
     long long log_cap;
     long long t;          // sweeps done
     long long slot;       // t % log_cap
     long long t_end;      // run while t < t_end
-    long long flip;       // the state of time t is in buf[(t + flip) & 1]; 0 but between two launches of two sweeps
     uint32_t key0, key1;  // Philox key = seed
     int L, N, T;          // T = L / D
     int nbx;              // blocks along x (block path)
     int nblocks;          // blocks of this surface (block path)
     int block_start;      // first global block index of this surface
-    int nbx2, nblocks2, block_start2;  // the same for the launches of two sweeps, whose blocks have a shape of their own
+    int block_start2;     // the same for the launches of two sweeps, whose blocks have a shape of their own
+    // kFlip: the state of time t is in buf[(t + 1) & 1] (between two launches
+    // of two sweeps only); kOwnSums: the record of the start is a caller's
+    // (lds_run takes S1 and S2 from the lattice)
+    uint32_t mode;
 };
+constexpr uint32_t kFlip = 1, kOwnSums = 2;
 
 template <int D>
 struct TileBits {
@@ -751,7 +755,7 @@ __device__ __forceinline__ void finish_sweep(SurfDev &d, long long t)
         __hip_atomic_store((gu64 *)(d.acc + kDoneWord), 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         *(gi64 *)&d.t = t + NS;
         *(gi64 *)&d.slot = slot;
-        if (NS == 2) *(gi64 *)&d.flip = d.flip ^ 1;
+        if (NS == 2) *(gint32 *)&d.mode = (int32_t)(d.mode ^ kFlip);
     }
 }
 
@@ -1162,7 +1166,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(
 // holds their corner site.
 //
 // Each launch changes buffers, so a pair of sweeps leaves the state in the
-// buffer of the wrong parity and the next pair brings it back (flip): the
+// buffer of the wrong parity and the next pair brings it back (kFlip): the
 // host launches this kernel twice, for four sweeps that every surface makes.
 //
 // Host requirements as for region_sweep with the larger region (L at least
@@ -1295,7 +1299,7 @@ struct PairSteps {
 template <int D, int TX, int TY, int NT, typename E, bool STEPS, int U = 8>
 __device__ __forceinline__ bool region_sweep2(E *lds, SurfDev &d, BlockPos bp, long long t, uint32_t flip, int ox0,
                                               int oy0, int ox1, int oy1, int *s_bad, long long (&inc)[4],
-                                              bool commit_here, int b)
+                                              bool commit_here, int b, int nblocks)
 {
     constexpr int W0 = TX + kTwoMargin;
     using G = BlockGeom<D, W0, TY + kTwoMargin>;
@@ -1418,12 +1422,12 @@ __device__ __forceinline__ bool region_sweep2(E *lds, SurfDev &d, BlockPos bp, l
     unsigned long long before = 0;
     if (commit_here) before = commit_sweep<NT, 2>(d, b, inc);
     if (commit_here && !STEPS) {
-        last = is_last(d.nblocks2, before);
+        last = is_last(nblocks, before);
         __syncthreads();
     }
     store_block<D, TX, TY, NT, E, PP>(lds, off + cx, RING + cy, gxa + off + cx >= L ? gxa - L : gxa, gy0 + RING + cy, L,
                                       hout, ref);
-    if (commit_here && STEPS) last = is_last(d.nblocks2, before);
+    if (commit_here && STEPS) last = is_last(nblocks, before);
     if (last) finish_sweep<false, 2>(d, t);
     return true;
 }
@@ -1446,28 +1450,29 @@ __global__ __launch_bounds__(NT) void block_sweep2(SurfDev *__restrict__ descs, 
     const int lb = block_map(blockIdx.x, gridDim.x, xmode, xnbx);
     SurfDev &d = descs[find_surface<true>(descs, nsurf, owner, lb)];
     const long long t = d.t;
-    const uint32_t flip = (uint32_t)d.flip;
+    const uint32_t flip = d.mode & kFlip;
     const u32x4 org0 = philox4x32_10(0u, 0u, (uint32_t)t, 2u, d.key0, d.key1);
     const u32x4 org1 = philox4x32_10(0u, 0u, (uint32_t)t + 1u, 2u, d.key0, d.key1);
     const int ox0 = (int)(org0.v[0] % (2u * D)), oy0 = (int)(org0.v[1] % (2u * D));
     const int ox1 = (int)(org1.v[0] % (2u * D)), oy1 = (int)(org1.v[1] % (2u * D));
     const int b = lb - d.block_start2;
-    const BlockPos bp = block_pos<TX, TY>(b % d.nbx2, b / d.nbx2, d.T);
+    const int nbx = (d.T + TX - 1) / TX, nblocks = nbx * ((d.T + TY - 1) / TY);
+    const BlockPos bp = block_pos<TX, TY>(b % nbx, b / nbx, d.T);
     long long inc[4] = {0, 0, 0, 0};
     if constexpr (STEPS) PairSteps<D, TX, TY, NT>::clear((int16_t *)lds_raw, d.N);
     __syncthreads();  // s_bad (and the counts of steps) cleared
     if constexpr (STEPS) {
         region_sweep2<D, TX, TY, NT, int16_t, true>((int16_t *)lds_raw, d, bp, t, flip, ox0, oy0, ox1, oy1, &s_bad, inc,
-                                                    true, b);
+                                                    true, b, nblocks);
     } else if (__builtin_expect(!region_sweep2<D, TX, TY, NT, int8_t, false>((int8_t *)lds_raw, d, bp, t, flip, ox0, oy0,
-                                                                            ox1, oy1, &s_bad, inc, true, b), 0)) {
+                                                                            ox1, oy1, &s_bad, inc, true, b, nblocks), 0)) {
 #pragma unroll 1
         for (int i = 0; i < 4; ++i) {
             const int sx = (i & 1) * (TX / 2), sy = (i >> 1) * (TY / 2);
             __syncthreads();  // the previous stores have read the LDS
             region_sweep2<D, TX / 2, TY / 2, NT, int16_t, false, 4>((int16_t *)lds_raw, d,
                                                                     BlockPos{bp.tx + sx, bp.ty + sy, bp.dupx - sx, bp.dupy - sy},
-                                                                    t, flip, ox0, oy0, ox1, oy1, &s_bad, inc, i == 3, b);
+                                                                    t, flip, ox0, oy0, ox1, oy1, &s_bad, inc, i == 3, b, nblocks);
         }
     }
 }
@@ -1939,24 +1944,12 @@ __global__ __launch_bounds__(NT) void lds_run(SurfDev *__restrict__ descs, const
     int ox, oy;
     origin(t, ox, oy);
     int base;
-    // thread 0 keeps the sums, from those of the lattice itself (the record
-    // of the start may be a caller's)
-    __shared__ long long s_start[2][NT / 64];
-    long long S1 = 0, S2 = 0, slot = d.slot;
     {
         const int32_t *src = d.buf[t & 1];
         base = src[0];
         for (int i = tid; i < L * L; i += NT) {
-            const int y = i / L, x = i - y * L, v = src[i];
-            h[(y < oy ? y + L : y) * P + (x < ox ? x + L : x)] = (int16_t)(v - base);
-            S1 += v;
-            S2 += (long long)v * v;
-        }
-        S1 = wave_sum63_64(S1);
-        S2 = wave_sum63_64(S2);
-        if ((tid & 63) == 63) {
-            s_start[0][tid >> 6] = S1;
-            s_start[1][tid >> 6] = S2;
+            const int y = i / L, x = i - y * L;
+            h[(y < oy ? y + L : y) * P + (x < ox ? x + L : x)] = (int16_t)(src[i] - base);
         }
         for (int i = tid; i < 2 * TB::NCALL * GROUPS; i += NT) (&s_steps[0][0][0])[i] = 0;
         if (tid < 4) s_sum[tid >> 1][tid & 1] = 0;
@@ -1965,14 +1958,34 @@ __global__ __launch_bounds__(NT) void lds_run(SurfDev *__restrict__ descs, const
             idle[-1] = idle[1] = idle[-P] = idle[P] = (int16_t)-N;
         }
     }
-    __syncthreads();
-    if (tid == 0) {
+    // thread 0 keeps the sums
+    long long S1 = 0, S2 = 0, slot = d.slot;
+    if (d.mode & kOwnSums) {
+        __shared__ long long s_start[2][NT / 64];
+        const int32_t *src = d.buf[t & 1];
+        for (int i = tid; i < L * L; i += NT) {
+            const long long v = src[i];
+            S1 += v;
+            S2 += v * v;
+        }
+        S1 = wave_sum63_64(S1);
+        S2 = wave_sum63_64(S2);
+        if ((tid & 63) == 63) {
+            s_start[0][tid >> 6] = S1;
+            s_start[1][tid >> 6] = S2;
+        }
+        __syncthreads();
         S1 = S2 = 0;
         for (int w = 0; w < NT / 64; ++w) {
             S1 += s_start[0][w];
             S2 += s_start[1][w];
         }
+    } else if (tid == 0) {
+        const long long *rec = d.log + 3 * slot;
+        S1 = rec[0];
+        S2 = rec[1];
     }
+    __syncthreads();
 
     const float r_half = 1.0f / (float)(T / 2), r_tiles = 1.0f / (float)ntiles, r_all = 1.0f / (float)all;
     // tile k of phase p: its place in the window, in tiles
