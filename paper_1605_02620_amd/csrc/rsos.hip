@@ -58,8 +58,10 @@ constexpr size_t kStagingBytes = 4096;      // least size of a pinned staging bu
 constexpr long long kReadRecords = 1 << 15; // most log records copied at once (768 KiB pinned)
 
 // ---------------------------------------------------------------------------
-// Block-kernel variants.  The tile block shape never changes results; it
-// only has to tile the lattice: T % TX == 0, T % TY == 0, region <= L.
+// Block-kernel variants.  The tile block shape never changes results.  On
+// int32 storage a shape serves every lattice of at least its tiles and its
+// region's sites a side (where it does not divide them, the last blocks
+// overlap the ones before); on 16-bit storage T % TX == 0 and T % TY == 0.
 // ---------------------------------------------------------------------------
 // e0 / e1: events recorded by the runtime when the kernel starts / ends
 // (hipExtLaunchKernel), for the timing mode; nullptr otherwise.

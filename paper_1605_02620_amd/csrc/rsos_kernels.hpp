@@ -29,8 +29,11 @@
 //                again by the same workgroup as int16 sub-blocks.
 //   block_sweep16  the same on heights kept in HBM as 16-bit residues
 //                (half the bytes per sweep) when N L <= 32766.
-//   lds_run      a whole small surface (L^2 * 4 bytes fits in LDS) lives in
-//                one workgroup's LDS for many sweeps; no per-sweep launch.
+//   block_sweep2   two sweeps in one pass over the lattice, for launches that
+//                are bound by their latency.
+//   lds_run, lds_run32   a whole small surface (L^2 * 4 bytes fits in LDS)
+//                lives in one workgroup's LDS for many sweeps; no per-sweep
+//                launch.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -673,8 +676,9 @@ struct BlockSteps {
     }
 };
 
-// Schedule selector: 0 = tile checkerboard, 1 = double tiling, 2 = checkerboard
-// in steps (int16 staging).
+// Schedule selector: 0 = tile checkerboard, 1 = double tiling.  (The kernels'
+// schedule 2, the checkerboard in steps on int16 staging, has its phases in
+// BlockSteps.)
 template <int SCHED, int D, int TX, int TY, int NT, int RWL, typename E, typename Q>
 __device__ __forceinline__ void sweep_phases(E *lds, int off, BlockPos bp, int T, uint32_t s, int N,
                                              uint32_t k0, uint32_t k1, int &acc, Q &q)
@@ -1856,7 +1860,8 @@ __global__ void unpack16(const uint16_t *__restrict__ src, int32_t *__restrict__
 // after each other.  So the attempts are made in steps (four lanes per tile);
 // for L <= 64 the waves that would idle lay the steps out, one sweep ahead.
 // Steps of eight would be about 20 at twice the lanes, which L = 128 does not
-// have idle.
+// have idle.  Many surfaces are bound by how many are resident: the host then
+// leaves the lists ahead out (may_ahead) or takes lds_run32 (lds_plan).
 //
 // Heights are staged as 16-bit offsets from a base that follows the surface
 // (the restriction keeps the spread below N L, the mean rises by at most one
