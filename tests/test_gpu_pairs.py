@@ -101,3 +101,18 @@ def test_uneven_call_captures_nothing(rsos):
 
     print("[pairs] runtime calls of uneven calls", flush=True)
     assert calls(0) <= calls(1) + 3  # a rewrite of the descriptors is three
+
+
+@pytest.mark.parametrize("L,N,start", [(144, 1, "flat"), (160, 2, "rough"), (144, 140, "cone"), (144, 141, "cone")])
+def test_pairs_on_the_smallest_lattices(rsos, oracle, L, N, start):
+    """The smallest sides of the tile-block path, whose regions are nearly as
+    wide as the lattice, up to the largest N of the 16-bit staging and one
+    more (single sweeps)."""
+    print(f"[pairs] L={L} N={N} {start}", flush=True)
+    h0 = (workloads.flat(L) if start == "flat" else workloads.cone(L, N, N * L // 4, seed=L) if start == "cone"
+          else workloads.rough(L, min(N, 4), seed=L))
+    s = rsos.Surface(L, N=N, seed=L + N, h0=h0)
+    assert s.kernel_name().startswith("block_sweep2<8,8,8,512,true>") == (N <= 140)
+    s.sweep(9)
+    _check(oracle, s.log(1, 9), s.heights(), h0, L, N, L + N, 0, 9, f"L={L} N={N}")
+    s.close()
