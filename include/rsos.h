@@ -420,15 +420,15 @@ rsos_status rsos_engine_destroy(rsos_engine *e);
 /* (device, D, L, N, storage and schedule flags, alone or batched), the    */
 /* launch knobs that leave every result unchanged: the tile-block variant  */
 /* (block shape, threads per workgroup, LDS staging type; one sweep per    */
-/* launch or two), the order in which workgroups take blocks across the 8  */
-/* XCDs, and the sweeps per captured hipGraph.  What is chosen or entered  */
-/* is what runs.  It times every candidate with HIP events on a       */
-/* scratch workload of the key (flat surfaces; one surface when alone,     */
-/* ceil(2^24 / L^2) surfaces in one launch when batched; L > 16384 tuned   */
-/* on a 16384^2 stand-in) and caches the fastest for the process.  Tuning */
-/* allocates scratch device memory (two int32 pools of the workload) and   */
-/* synchronises; it never touches a caller's surface.  The cache is        */
-/* process-wide and guarded by a mutex.                                    */
+/* launch or, alone and for few blocks, two), the order in which           */
+/* workgroups take blocks across the 8 XCDs, and the sweeps per captured   */
+/* hipGraph. What is chosen or entered is what runs.  It times every       */
+/* candidate with HIP events on a scratch workload of the key (flat        */
+/* surfaces; one surface when alone, ceil(2^24 / L^2) surfaces in one      */
+/* launch when batched; L > 16384 tuned on a 16384^2 stand-in) and caches  */
+/* the fastest for the process.  Tuning allocates scratch device memory    */
+/* (two int32 pools of the workload) and synchronises; it never touches a  */
+/* caller's surface.  The cache is process-wide and guarded by a mutex.    */
 /* --------------------------------------------------------------------- */
 
 /* One launch configuration.
@@ -447,8 +447,9 @@ rsos_status rsos_engine_destroy(rsos_engine *e);
  *                 entered by rsos_tune_set (or loaded as such);
  *   ms_per_sweep  the chosen configuration's mean sweep time on the
  *                 tuning workload (0 if not measured);
- *   ms_first_fit  the untuned default's (two sweeps per launch or the first
- *                 fitting variant, xmode 1) on the same workload. */
+ *   ms_first_fit  the untuned default's (alone, two sweeps per launch where
+ *                 few blocks make that the default; else the first fitting
+ *                 variant; xmode 1) on the same workload. */
 #define RSOS_TUNE_PAIR 64
 typedef struct {
     int32_t TX, TY, NT, elem;

@@ -269,21 +269,25 @@ bool pair_fits(const Pair &q, int L, int N)
     return (q.steps || 2ll * N * q.D <= 96) && (long long)N * (rw + rh + 4) + 2 * q.D * q.D <= 32767;
 }
 
+// Whether row q takes the surfaces (L, N) in one launch.
+bool pair_takes(const Pair &q, const std::vector<std::pair<int, int>> &LN)
+{
+    bool ok = true;
+    long long blocks = 0;
+    for (auto &ln : LN) {
+        ok = ok && pair_fits(q, ln.first, ln.second);
+        blocks += (long long)blocks_along(ln.first / q.D, q.TX) * blocks_along(ln.first / q.D, q.TY);
+    }
+    return ok && blocks <= q.per_cu * kCUs;
+}
+
 // The shape for two sweeps per launch of surfaces (L, N), or nullptr (also
 // where RSOS_VARIANT names the kernel to run).
 const Pair *pick_pair(int D, const std::vector<std::pair<int, int>> &LN)
 {
     if (getenv("RSOS_VARIANT")) return nullptr;
-    for (const Pair &q : kPairs) {
-        if (q.D != D) continue;
-        bool ok = true;
-        long long blocks = 0;
-        for (auto &ln : LN) {
-            ok = ok && pair_fits(q, ln.first, ln.second);
-            blocks += (long long)blocks_along(ln.first / D, q.TX) * blocks_along(ln.first / D, q.TY);
-        }
-        if (ok && blocks <= q.per_cu * kCUs) return &q;
-    }
+    for (const Pair &q : kPairs)
+        if (q.D == D && pair_takes(q, LN)) return &q;
     return nullptr;
 }
 

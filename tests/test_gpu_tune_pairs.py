@@ -93,3 +93,11 @@ def test_tuned_is_not_slower_than_the_default(surface):
     print(f"[tune] {t}", flush=True)
     # (ties within 1% go to the column strips)
     assert t["measured"] == 1 and t["ms_first_fit"] > 0 and t["ms_per_sweep"] <= 1.0101 * t["ms_first_fit"]
+
+
+@pytest.mark.parametrize("L,batch,pairs", [(512, False, True), (4096, False, True), (8192, False, False), (512, True, False)])
+def test_pairs_are_timed_where_launches_are_small(surface, L, batch, pairs):
+    """Two sweeps per launch are a candidate alone, and where the blocks are
+    few enough for the untuned rule to take them."""
+    print(f"[tune] candidates L={L} batch={batch}", flush=True)
+    assert any(c["elem"] & PAIR for c in surface.tune_candidates(L, 1, 8, batch=batch)) == pairs
