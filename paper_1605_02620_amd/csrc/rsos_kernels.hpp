@@ -730,9 +730,10 @@ __device__ __forceinline__ long long wave_sum63_64(long long v)
     return v;
 }
 
-// Wave 0 of the block that completed the count of a launch of NS sweeps.
+// Wave 0 of the block that completed the count of a launch of NS sweeps (of
+// two: mode is the descriptor's).
 template <bool MEAN, int NS = 1>
-__device__ __forceinline__ void finish_sweep(SurfDev &d, long long t)
+__device__ __forceinline__ void finish_sweep(SurfDev &d, long long t, uint32_t mode = 0)
 {
     const int lane = threadIdx.x;  // < 64
     const gi64 *prev = (const gi64 *)(d.log + 3 * d.slot);
@@ -759,7 +760,7 @@ __device__ __forceinline__ void finish_sweep(SurfDev &d, long long t)
         __hip_atomic_store((gu64 *)(d.acc + kDoneWord), 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         *(gi64 *)&d.t = t + NS;
         *(gi64 *)&d.slot = slot;
-        if (NS == 2) *(gint32 *)&d.mode = (int32_t)(d.mode ^ kFlip);
+        if (NS == 2) *(gint32 *)&d.mode = (int32_t)(mode ^ kFlip);
     }
 }
 
@@ -1301,7 +1302,7 @@ struct PairSteps {
 };
 
 template <int D, int TX, int TY, int NT, typename E, bool STEPS, int U = 8>
-__device__ __forceinline__ bool region_sweep2(E *lds, SurfDev &d, BlockPos bp, long long t, uint32_t flip, int ox0,
+__device__ __forceinline__ bool region_sweep2(E *lds, SurfDev &d, BlockPos bp, long long t, uint32_t mode, int ox0,
                                               int oy0, int ox1, int oy1, int *s_bad, long long (&inc)[4],
                                               bool commit_here, int b, int nblocks)
 {
@@ -1312,6 +1313,7 @@ __device__ __forceinline__ bool region_sweep2(E *lds, SurfDev &d, BlockPos bp, l
     const uint32_t s = (uint32_t)t;
     const int L = d.L, N = d.N, T = d.T;
     const uint32_t k0 = d.key0, k1 = d.key1;
+    const uint32_t flip = mode & kFlip;
     const gint32 *__restrict__ hin = as_global(d.buf[(s + flip) & 1u]);
     gint32 *__restrict__ hout = as_global(d.buf[(s + flip + 1u) & 1u]);
 
@@ -1432,7 +1434,7 @@ __device__ __forceinline__ bool region_sweep2(E *lds, SurfDev &d, BlockPos bp, l
     store_block<D, TX, TY, NT, E, PP>(lds, off + cx, RING + cy, gxa + off + cx >= L ? gxa - L : gxa, gy0 + RING + cy, L,
                                       hout, ref);
     if (commit_here && STEPS) last = is_last(nblocks, before);
-    if (last) finish_sweep<false, 2>(d, t);
+    if (last) finish_sweep<false, 2>(d, t, mode);
     return true;
 }
 
@@ -1454,21 +1456,21 @@ __global__ __launch_bounds__(NT) void block_sweep2(SurfDev *__restrict__ descs, 
     const int lb = block_map(blockIdx.x, gridDim.x, xmode, xnbx);
     SurfDev &d = descs[find_surface<true>(descs, nsurf, owner, lb)];
     const long long t = d.t;
-    const uint32_t flip = d.mode & kFlip;
+    const uint32_t mode = d.mode;
     const u32x4 org0 = philox4x32_10(0u, 0u, (uint32_t)t, 2u, d.key0, d.key1);
     const u32x4 org1 = philox4x32_10(0u, 0u, (uint32_t)t + 1u, 2u, d.key0, d.key1);
     const int ox0 = (int)(org0.v[0] % (2u * D)), oy0 = (int)(org0.v[1] % (2u * D));
     const int ox1 = (int)(org1.v[0] % (2u * D)), oy1 = (int)(org1.v[1] % (2u * D));
     const int b = lb - d.block_start2;
-    const int nbx = (d.T + TX - 1) / TX, nblocks = nbx * ((d.T + TY - 1) / TY);
+    const int nbx = xnbx ? xnbx : (d.T + TX - 1) / TX, nblocks = nbx * ((d.T + TY - 1) / TY);
     const BlockPos bp = block_pos<TX, TY>(b % nbx, b / nbx, d.T);
     long long inc[4] = {0, 0, 0, 0};
     if constexpr (STEPS) PairSteps<D, TX, TY, NT>::clear((int16_t *)lds_raw, d.N);
     __syncthreads();  // s_bad (and the counts of steps) cleared
     if constexpr (STEPS) {
-        region_sweep2<D, TX, TY, NT, int16_t, true>((int16_t *)lds_raw, d, bp, t, flip, ox0, oy0, ox1, oy1, &s_bad, inc,
+        region_sweep2<D, TX, TY, NT, int16_t, true>((int16_t *)lds_raw, d, bp, t, mode, ox0, oy0, ox1, oy1, &s_bad, inc,
                                                     true, b, nblocks);
-    } else if (__builtin_expect(!region_sweep2<D, TX, TY, NT, int8_t, false>((int8_t *)lds_raw, d, bp, t, flip, ox0, oy0,
+    } else if (__builtin_expect(!region_sweep2<D, TX, TY, NT, int8_t, false>((int8_t *)lds_raw, d, bp, t, mode, ox0, oy0,
                                                                             ox1, oy1, &s_bad, inc, true, b, nblocks), 0)) {
 #pragma unroll 1
         for (int i = 0; i < 4; ++i) {
@@ -1476,7 +1478,7 @@ __global__ __launch_bounds__(NT) void block_sweep2(SurfDev *__restrict__ descs, 
             __syncthreads();  // the previous stores have read the LDS
             region_sweep2<D, TX / 2, TY / 2, NT, int16_t, false, 4>((int16_t *)lds_raw, d,
                                                                     BlockPos{bp.tx + sx, bp.ty + sy, bp.dupx - sx, bp.dupy - sy},
-                                                                    t, flip, ox0, oy0, ox1, oy1, &s_bad, inc, i == 3, b, nblocks);
+                                                                    t, mode, ox0, oy0, ox1, oy1, &s_bad, inc, i == 3, b, nblocks);
         }
     }
 }
