@@ -216,7 +216,7 @@ rsos_status rsos_timing_read(rsos_surface *s, int64_t *launches, double *mean_ms
  * schedule: 0 checkerboard, 1 double tiling, 2 checkerboard with attempts in
  * steps), "block_sweep16<8,32,8,256,0>" with 16-bit storage,
  * "block_sweep2<8,32,8,256,false>" (D, tiles, threads, attempts in steps)
- * where two sweeps share a launch, or "lds_run<8,512,0>" for an LDS-resident
+ * where two sweeps share a launch, or "lds_run<8,512,0,true>" for an LDS-resident
  * surface; written NUL-terminated into buf (at most len bytes).  With several
  * kernel instances (a tuned batch) the first one.  A surface that makes two
  * sweeps per launch makes the last one to three sweeps of a call by a

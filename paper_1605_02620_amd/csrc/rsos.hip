@@ -310,9 +310,9 @@ rsos_status check_packed(const rsos_params *p)
     return RSOS_OK;
 }
 
-// How a launch runs surfaces that live in LDS: attempts in steps (lds_run),
-// with the next sweep's steps laid out ahead where that is offered or with
-// one phase's at a time, or one lane per tile (lds_run32).
+// How a launch runs surfaces that live in LDS: attempts in steps, with the
+// next sweep's steps laid out ahead where that is offered or with one phase's
+// at a time (lds_run), or one lane per tile (lds_run32).
 enum class LdsMode { kAhead, kSteps, kLane };
 struct LdsPlan {
     LdsMode mode = LdsMode::kLane;
@@ -322,11 +322,13 @@ typedef void (*LdsLaunch)(dim3, const LdsPlan &, hipStream_t, SurfDev *, const i
 template <int D, int SCHED>
 void launch_lds(dim3 grid, const LdsPlan &pl, hipStream_t st, SurfDev *d, const int *w)
 {
+    constexpr int NT = rsosk::kLdsThreads;
     if (pl.mode == LdsMode::kLane)
         hipLaunchKernelGGL((rsosk::lds_run32<D, 256, SCHED>), grid, dim3(256), pl.bytes, st, d, w);
-    else if constexpr (D > 2)
-        hipLaunchKernelGGL((rsosk::lds_run<D, rsosk::kLdsThreads, SCHED>), grid, dim3(rsosk::kLdsThreads), pl.bytes, st, d, w,
-                           pl.mode == LdsMode::kAhead ? 1 : 0);
+    else if constexpr (D > 2) {
+        if (pl.mode == LdsMode::kAhead) hipLaunchKernelGGL((rsosk::lds_run<D, NT, SCHED>), grid, dim3(NT), pl.bytes, st, d, w);
+        else hipLaunchKernelGGL((rsosk::lds_run<D, NT, SCHED, false>), grid, dim3(NT), pl.bytes, st, d, w);
+    }
 }
 LdsLaunch lds_launcher(int D, int sched = 0)
 {
@@ -362,16 +364,13 @@ size_t lds_bytes_of(int D, int sched, int L, LdsMode mode)
 {
     if (mode == LdsMode::kLane) return (size_t)L * L * 4;
     const int ph = sched == 1 ? 4 : 2;
-    auto bytes = [&](auto run) -> size_t {
-        using R = decltype(run);
-        return (size_t)R::bytes(L, ph, mode == LdsMode::kAhead && R::ahead(L, ph));
-    };
+    const bool ahead = mode == LdsMode::kAhead;
     switch (D) {
-    case 4: return bytes(rsosk::LdsRun<4>());
-    case 8: return bytes(rsosk::LdsRun<8>());
-    case 16: return bytes(rsosk::LdsRun<16>());
+    case 4: return (size_t)(ahead ? rsosk::LdsRun<4>::bytes(L, ph) : rsosk::LdsRun<4, false>::bytes(L, ph));
+    case 8: return (size_t)(ahead ? rsosk::LdsRun<8>::bytes(L, ph) : rsosk::LdsRun<8, false>::bytes(L, ph));
+    case 16: return (size_t)(ahead ? rsosk::LdsRun<16>::bytes(L, ph) : rsosk::LdsRun<16, false>::bytes(L, ph));
     }
-    return bytes(rsosk::LdsRun<32>());
+    return (size_t)(ahead ? rsosk::LdsRun<32>::bytes(L, ph) : rsosk::LdsRun<32, false>::bytes(L, ph));
 }
 
 // What a sweep of one surface takes alone on its CU, by mode (us; columns:
@@ -1274,7 +1273,7 @@ rsos_status rsos_kernel_name(rsos_surface *s, char *buf, int32_t len)
         snprintf(buf, (size_t)len, "block_sweep<%d,%d,%d,%d,%s,%d>", v->D, v->TX, v->TY, v->NT,
                  v->elem == 1 ? "int8,int16" : v->elem == 2 ? "int16,void" : "int32,void", v->steps ? 2 : g.sched);
     else
-        snprintf(buf, (size_t)len, g.lds.mode == LdsMode::kLane ? "lds_run32<%d,256,%d>" : "lds_run<%d,512,%d>", g.D, g.sched);
+        snprintf(buf, (size_t)len, g.lds.mode == LdsMode::kLane ? "lds_run32<%d,256,%d>" : "lds_run<%d,512,%d,true>", g.D, g.sched);
     return RSOS_OK;
 }
 
@@ -1499,10 +1498,25 @@ rsos_status scratch_ptr(unsigned char **out)
 
 // Writes the descriptor, clears the accumulators and stores the record of
 // time t0 (a fill kernel, not a memset: callers may capture the launches).
-__global__ void static_setup(SurfDev d, unsigned char *base, long long s1, long long s2)
+// Surfaces in LDS (`sum`) get the sums of the lattice itself, whatever the
+// caller's are: lds_run goes on from the record, and lds_run32, which sums
+// the lattice after each sweep, does not need it.
+__global__ __launch_bounds__(256) void static_setup(SurfDev d, unsigned char *base, long long s1, long long s2, int sum)
 {
     long long *acc = (long long *)(base + kScratchAcc);
     for (int i = threadIdx.x; i < rsosk::kAccWords; i += blockDim.x) acc[i] = 0;
+    if (sum) {
+        long long unused = 0;
+        s1 = s2 = 0;
+        const int32_t *h = d.buf[d.t & 1];
+        for (int i = threadIdx.x; i < d.L * d.L; i += 256) {
+            const long long v = h[i];
+            s1 += v;
+            s2 += v * v;
+        }
+        rsosk::block_reduce3<256>(s1, s2, unused);
+    }
+    __syncthreads();  // the accumulators are clear
     if (threadIdx.x == 0) {
         *(int *)(base + kScratchIdx) = 0;
         const long long L2 = (long long)d.L * d.L;
@@ -1556,7 +1570,6 @@ extern "C" rsos_status rsos_sweep_static(const rsos_params *p, int32_t *d_h, int
     d.t = t0;
     d.slot = t0 % kStaticLogCap;
     d.t_end = t0 + n_mcs;
-    d.mode = rsosk::kOwnSums;
     d.key0 = (uint32_t)(p->seed & 0xFFFFFFFFu);
     d.key1 = (uint32_t)(p->seed >> 32);
     d.L = p->L;
@@ -1574,7 +1587,7 @@ extern "C" rsos_status rsos_sweep_static(const rsos_params *p, int32_t *d_h, int
     }
     hipStream_t s = (hipStream_t)stream;
     SurfDev *dd = (SurfDev *)(base + kScratchDesc);
-    hipLaunchKernelGGL(static_setup, dim3(1), dim3(256), 0, s, d, base, (long long)s1, (long long)s2);
+    hipLaunchKernelGGL(static_setup, dim3(1), dim3(256), 0, s, d, base, (long long)s1, (long long)s2, v ? 0 : 1);
     HIP_TRY(hipGetLastError());
     if (!v) {
         // the whole surface in one workgroup's LDS, all sweeps in one launch

@@ -119,25 +119,21 @@ __device__ __forceinline__ void store4(gint32 *p, const int4 v)
 }
 
 struct SurfDev {
-    int32_t *buf[2];      // state after t sweeps is in buf[t & 1] (see mode)
+    int32_t *buf[2];      // state after t sweeps is in buf[t & 1] (see flip)
     long long *log;       // 3 * log_cap int64: (S1, S2, A) of time tau at slot tau % log_cap
     long long *acc;       // kAccWords int64: accumulators (zero between sweeps), mean floor
     long long log_cap;
     long long t;          // sweeps done
     long long slot;       // t % log_cap
     long long t_end;      // run while t < t_end
+    uint32_t flip;        // the state of time t is in buf[(t + flip) & 1]; 0 but between two launches of two sweeps
+    int block_start2;     // as block_start for the launches of two sweeps, whose blocks have a shape of their own
     uint32_t key0, key1;  // Philox key = seed
     int L, N, T;          // T = L / D
     int nbx;              // blocks along x (block path)
     int nblocks;          // blocks of this surface (block path)
     int block_start;      // first global block index of this surface
-    int block_start2;     // the same for the launches of two sweeps, whose blocks have a shape of their own
-    // kFlip: the state of time t is in buf[(t + 1) & 1] (between two launches
-    // of two sweeps only); kOwnSums: the record of the start is a caller's
-    // (lds_run takes S1 and S2 from the lattice)
-    uint32_t mode;
 };
-constexpr uint32_t kFlip = 1, kOwnSums = 2;
 
 template <int D>
 struct TileBits {
@@ -731,9 +727,9 @@ __device__ __forceinline__ long long wave_sum63_64(long long v)
 }
 
 // Wave 0 of the block that completed the count of a launch of NS sweeps (of
-// two: mode is the descriptor's).
+// two: flip is the descriptor's).
 template <bool MEAN, int NS = 1>
-__device__ __forceinline__ void finish_sweep(SurfDev &d, long long t, uint32_t mode = 0)
+__device__ __forceinline__ void finish_sweep(SurfDev &d, long long t, uint32_t flip = 0)
 {
     const int lane = threadIdx.x;  // < 64
     const gi64 *prev = (const gi64 *)(d.log + 3 * d.slot);
@@ -760,7 +756,7 @@ __device__ __forceinline__ void finish_sweep(SurfDev &d, long long t, uint32_t m
         __hip_atomic_store((gu64 *)(d.acc + kDoneWord), 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         *(gi64 *)&d.t = t + NS;
         *(gi64 *)&d.slot = slot;
-        if (NS == 2) *(gint32 *)&d.mode = (int32_t)(mode ^ kFlip);
+        if (NS == 2) *(gint32 *)&d.flip = (int32_t)(flip ^ 1u);
     }
 }
 
@@ -1171,7 +1167,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(
 // holds their corner site.
 //
 // Each launch changes buffers, so a pair of sweeps leaves the state in the
-// buffer of the wrong parity and the next pair brings it back (kFlip): the
+// buffer of the wrong parity and the next pair brings it back (flip): the
 // host launches this kernel twice, for four sweeps that every surface makes.
 //
 // Host requirements as for region_sweep with the larger region (L at least
@@ -1302,7 +1298,7 @@ struct PairSteps {
 };
 
 template <int D, int TX, int TY, int NT, typename E, bool STEPS, int U = 8>
-__device__ __forceinline__ bool region_sweep2(E *lds, SurfDev &d, BlockPos bp, long long t, uint32_t mode, int ox0,
+__device__ __forceinline__ bool region_sweep2(E *lds, SurfDev &d, BlockPos bp, long long t, uint32_t flip, int ox0,
                                               int oy0, int ox1, int oy1, int *s_bad, long long (&inc)[4],
                                               bool commit_here, int b, int nblocks)
 {
@@ -1313,7 +1309,6 @@ __device__ __forceinline__ bool region_sweep2(E *lds, SurfDev &d, BlockPos bp, l
     const uint32_t s = (uint32_t)t;
     const int L = d.L, N = d.N, T = d.T;
     const uint32_t k0 = d.key0, k1 = d.key1;
-    const uint32_t flip = mode & kFlip;
     const gint32 *__restrict__ hin = as_global(d.buf[(s + flip) & 1u]);
     gint32 *__restrict__ hout = as_global(d.buf[(s + flip + 1u) & 1u]);
 
@@ -1434,7 +1429,7 @@ __device__ __forceinline__ bool region_sweep2(E *lds, SurfDev &d, BlockPos bp, l
     store_block<D, TX, TY, NT, E, PP>(lds, off + cx, RING + cy, gxa + off + cx >= L ? gxa - L : gxa, gy0 + RING + cy, L,
                                       hout, ref);
     if (commit_here && STEPS) last = is_last(nblocks, before);
-    if (last) finish_sweep<false, 2>(d, t, mode);
+    if (last) finish_sweep<false, 2>(d, t, flip);
     return true;
 }
 
@@ -1456,7 +1451,7 @@ __global__ __launch_bounds__(NT) void block_sweep2(SurfDev *__restrict__ descs, 
     const int lb = block_map(blockIdx.x, gridDim.x, xmode, xnbx);
     SurfDev &d = descs[find_surface<true>(descs, nsurf, owner, lb)];
     const long long t = d.t;
-    const uint32_t mode = d.mode;
+    const uint32_t flip = d.flip;
     const u32x4 org0 = philox4x32_10(0u, 0u, (uint32_t)t, 2u, d.key0, d.key1);
     const u32x4 org1 = philox4x32_10(0u, 0u, (uint32_t)t + 1u, 2u, d.key0, d.key1);
     const int ox0 = (int)(org0.v[0] % (2u * D)), oy0 = (int)(org0.v[1] % (2u * D));
@@ -1468,9 +1463,9 @@ __global__ __launch_bounds__(NT) void block_sweep2(SurfDev *__restrict__ descs, 
     if constexpr (STEPS) PairSteps<D, TX, TY, NT>::clear((int16_t *)lds_raw, d.N);
     __syncthreads();  // s_bad (and the counts of steps) cleared
     if constexpr (STEPS) {
-        region_sweep2<D, TX, TY, NT, int16_t, true>((int16_t *)lds_raw, d, bp, t, mode, ox0, oy0, ox1, oy1, &s_bad, inc,
+        region_sweep2<D, TX, TY, NT, int16_t, true>((int16_t *)lds_raw, d, bp, t, flip, ox0, oy0, ox1, oy1, &s_bad, inc,
                                                     true, b, nblocks);
-    } else if (__builtin_expect(!region_sweep2<D, TX, TY, NT, int8_t, false>((int8_t *)lds_raw, d, bp, t, mode, ox0, oy0,
+    } else if (__builtin_expect(!region_sweep2<D, TX, TY, NT, int8_t, false>((int8_t *)lds_raw, d, bp, t, flip, ox0, oy0,
                                                                             ox1, oy1, &s_bad, inc, true, b, nblocks), 0)) {
 #pragma unroll 1
         for (int i = 0; i < 4; ++i) {
@@ -1478,7 +1473,7 @@ __global__ __launch_bounds__(NT) void block_sweep2(SurfDev *__restrict__ descs, 
             __syncthreads();  // the previous stores have read the LDS
             region_sweep2<D, TX / 2, TY / 2, NT, int16_t, false, 4>((int16_t *)lds_raw, d,
                                                                     BlockPos{bp.tx + sx, bp.ty + sy, bp.dupx - sx, bp.dupy - sy},
-                                                                    t, mode, ox0, oy0, ox1, oy1, &s_bad, inc, i == 3, b, nblocks);
+                                                                    t, flip, ox0, oy0, ox1, oy1, &s_bad, inc, i == 3, b, nblocks);
         }
     }
 }
@@ -1863,7 +1858,7 @@ __global__ void unpack16(const uint16_t *__restrict__ src, int32_t *__restrict__
 // for L <= 64 the waves that would idle lay the steps out, one sweep ahead.
 // Steps of eight would be about 20 at twice the lanes, which L = 128 does not
 // have idle.  Many surfaces are bound by how many are resident: the host then
-// leaves the lists ahead out (may_ahead) or takes lds_run32 (lds_plan).
+// leaves the lists ahead out (AHEAD) or takes lds_run32 (lds_plan).
 //
 // Heights are staged as 16-bit offsets from a base that follows the surface
 // (the restriction keeps the spread below N L, the mean rises by at most one
@@ -1881,7 +1876,7 @@ constexpr int kLdsRebase = 4096;  // sweeps between moves of the base: 2 N L + k
 constexpr int kLdsMaxL = 128;
 constexpr int kLdsThreads = 512;  // four lanes for each of the 128 tiles of a phase at L = 128, D = 8
 
-template <int D>
+template <int D, bool AHEAD = true>
 struct LdsRun {
     using TB = TileBits<D>;
     // one row pitch for every L: the neighbours of a site are at constant
@@ -1895,25 +1890,27 @@ struct LdsRun {
     __host__ __device__ static int lattice_bytes(int L) { return (lattice_rows(L) * P * 2 + 15) & ~15; }
     // Small lattices leave waves without an attempt to make: these lay out
     // the next sweep's steps (all phases) meanwhile, into a second set of
-    // lists.  The others lay out one phase at a time, by all waves.
+    // lists.  The others (all, without AHEAD) lay out one phase at a time, by
+    // all waves.
     __host__ __device__ static bool ahead(int L, int phases)
     {
-        return L <= 64 && L / D * (L / D) / phases * kLdsWin <= kLdsThreads / 2;
+        return AHEAD && L <= 64 && L / D * (L / D) / phases * kLdsWin <= kLdsThreads / 2;
     }
-    __host__ __device__ static int list_bytes(int L, int phases, bool ahead)  // of one set
+    __host__ __device__ static int list_bytes(int L, int phases)  // of one set
     {
-        return L * L / (ahead ? 1 : phases) * kLdsWin * 2 + 16;  // one pair is read beyond the last
+        return L * L / (ahead(L, phases) ? 1 : phases) * kLdsWin * 2 + 16;  // one pair is read beyond the last
     }
-    __host__ __device__ static int bytes(int L, int phases, bool ahead)
+    __host__ __device__ static int bytes(int L, int phases)
     {
-        return lattice_bytes(L) + list_bytes(L, phases, ahead) * (ahead ? 2 : 1);
+        return lattice_bytes(L) + list_bytes(L, phases) * (ahead(L, phases) ? 2 : 1);
     }
 };
 
-template <int D, int NT, int SCHED = 0>
-__global__ __launch_bounds__(NT) void lds_run(SurfDev *__restrict__ descs, const int *__restrict__ which, int may_ahead)
+// AHEAD false: one phase's lists at a time for every L, less LDS.
+template <int D, int NT, int SCHED = 0, bool AHEAD = true>
+__global__ __launch_bounds__(NT) void lds_run(SurfDev *__restrict__ descs, const int *__restrict__ which)
 {
-    using R = LdsRun<D>;
+    using R = LdsRun<D, AHEAD>;
     using TB = TileBits<D>;
     constexpr int PH = SCHED == 0 ? 2 : 4, P = R::P;
     constexpr int MAXT = kLdsMaxL / D;
@@ -1930,14 +1927,14 @@ __global__ __launch_bounds__(NT) void lds_run(SurfDev *__restrict__ descs, const
     if (t >= t_end) return;
     const int L = d.L, N = d.N, T = d.T, tid = threadIdx.x;
     const uint32_t k0 = d.key0, k1 = d.key1;
-    const bool ahead = may_ahead && R::ahead(L, PH);
+    const bool ahead = R::ahead(L, PH);
     const int ntiles = T * T / PH, ngroups = (ntiles + 15) / 16;
     const int all = ahead ? T * T : ntiles;   // tiles of a set of lists
     // threads that lay out steps while the others make attempts
     const int makers = min(NT, (ntiles * kLdsWin + 63) & ~63);
     int16_t *h = (int16_t *)lds_dyn + P + 1;  // site (0, 0); the frame's at index -1
     uint16_t *const lists = (uint16_t *)(lds_dyn + R::lattice_bytes(L));
-    const int set = R::list_bytes(L, PH, ahead) / 2;  // entries of a set
+    const int set = R::list_bytes(L, PH) / 2;  // entries of a set
     // a site that no attempt changes, for lanes without one: N above all its
     // neighbours
     int16_t *const idle = h + (L + 2 * D + 2) * P;  // row L + 2 D + 3 of the array
@@ -1967,27 +1964,7 @@ __global__ __launch_bounds__(NT) void lds_run(SurfDev *__restrict__ descs, const
     }
     // thread 0 keeps the sums
     long long S1 = 0, S2 = 0, slot = d.slot;
-    if (d.mode & kOwnSums) {
-        __shared__ long long s_start[2][NT / 64];
-        const int32_t *src = d.buf[t & 1];
-        for (int i = tid; i < L * L; i += NT) {
-            const long long v = src[i];
-            S1 += v;
-            S2 += v * v;
-        }
-        S1 = wave_sum63_64(S1);
-        S2 = wave_sum63_64(S2);
-        if ((tid & 63) == 63) {
-            s_start[0][tid >> 6] = S1;
-            s_start[1][tid >> 6] = S2;
-        }
-        __syncthreads();
-        S1 = S2 = 0;
-        for (int w = 0; w < NT / 64; ++w) {
-            S1 += s_start[0][w];
-            S2 += s_start[1][w];
-        }
-    } else if (tid == 0) {
+    if (tid == 0) {
         const long long *rec = d.log + 3 * slot;
         S1 = rec[0];
         S2 = rec[1];

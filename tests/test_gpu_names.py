@@ -7,7 +7,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("L,D,kw,name,timed", [
-    (64, 8, {}, "lds_run<8,512,0>", None),
+    (64, 8, {}, "lds_run<8,512,0,true>", None),
     (128, 2, {}, "lds_run32<2,256,0>", None),
     (256, 8, {}, "block_sweep2<8,8,8,512,true>", "block_sweep<8,8,8,256,int16,void,2>"),
     (1360, 8, {}, "block_sweep2<8,32,8,256,false>", "block_sweep<8,16,8,512,int16,void,2>"),
